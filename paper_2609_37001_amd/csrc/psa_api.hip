@@ -233,14 +233,13 @@ psa_status_t check_layout_args(const void* a, const void* b, int32_t n_bh, int32
   return PSA_OK;
 }
 
-int32_t persistent_workgroups() {
+// Compute units of the current device: the persistent grids are sized by them.
+int32_t compute_units() {
   int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (hipGetDevice(&dev) != hipSuccess) return 128;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    return 256;
-  // Two 4-wave workgroups per CU for the one-row engine (about 80 KB of LDS each); the pair engine
-  // (block 128) launches half as many 8-wave workgroups, one per CU.
-  return 2 * cus;
+    return 128;
+  return cus;
 }
 
 // The run of a plan; `rearm` = false right after the plan's own kernels, which leave the queue
@@ -259,7 +258,7 @@ psa_status_t run_planned(const void* q, const void* k, const void* v, void* o, i
   if (s != PSA_OK) return s;
   const float c = softmax_scale * 1.4426950408889634f;
   hipError_t e = psa::launch_sparse(q, k, v, o, lse, batch, n_heads, head_dim, g, c, workspace, wl,
-                                    persistent_workgroups(), stream, rearm);
+                                    compute_units(), stream, rearm);
   if (e != hipSuccess) return hip_fail(e, "psa_attention_run kernel launch");
   return PSA_OK;
 }
@@ -370,7 +369,7 @@ psa_status_t psa_attention_run_3d(const void* q, const void* k, const void* v, v
   if (s != PSA_OK) return s;
   const float c = softmax_scale * 1.4426950408889634f;
   hipError_t e = psa::launch_sparse(q, k, v, o, lse, batch, n_heads, head_dim, g, c, workspace, wl,
-                                    persistent_workgroups(), stream);
+                                    compute_units(), stream);
   if (e != hipSuccess) return hip_fail(e, "psa_attention_run_3d kernel launch");
   return PSA_OK;
 }
@@ -487,8 +486,8 @@ psa_status_t psa_dense_fwd(const void* q, const void* k, const void* v, void* o,
   if (((uintptr_t)workspace & 255) != 0)
     return fail(PSA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   const float c = softmax_scale * 1.4426950408889634f;
-  hipError_t e = psa::launch_dense(q, k, v, o, lse, batch, n_heads, head_dim, n_tokens, block, c,
-                                   (int32_t*)workspace, persistent_workgroups(), stream);
+  hipError_t e = psa::launch_dense(q, k, v, o, lse, batch, n_heads, head_dim, n_tokens, c,
+                                   (int32_t*)workspace, compute_units(), stream);
   if (e != hipSuccess) return hip_fail(e, "psa_dense_fwd kernel launch");
   return PSA_OK;
 }

@@ -63,7 +63,7 @@ constexpr int kCounterStride = 32;
 constexpr int kQueueCounters = 32;
 constexpr int kQueueWords = kQueueCounters + kNumQueues * kCounterStride;
 // Word of the first line (after the boundaries) counting the finished workgroups of the plan's
-// last kernel at block 128.
+// last kernel (psa_starts_kernel).
 constexpr int kStartsDone = 16;
 static_assert(kStartsDone > kNumQueues && kStartsDone < kQueueCounters, "free word of the first line");
 
@@ -128,14 +128,13 @@ hipError_t launch_schedule(const Geometry& g, int32_t batch, int32_t n_heads, vo
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
                          int32_t batch, int32_t n_heads, int32_t head_dim, const Geometry& g,
                          float scale_log2, void* workspace, const WorkspaceLayout& wl,
-                         int32_t n_workgroups, hipStream_t stream, bool rearm = true);
+                         int32_t cus, hipStream_t stream, bool rearm = true);
 
-// queues: the int32 [kQueueWords] queue area of a dense workspace (persistent grid of
-// n_workgroups one-row workgroups), or nullptr (one workgroup per work item).
+// queues: the int32 [kQueueWords] queue area of a dense workspace (persistent grid), or nullptr
+// (one workgroup per work item).
 hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, float* lse,
                         int32_t batch, int32_t n_heads, int32_t head_dim, int32_t n_tokens,
-                        int32_t block, float scale_log2, int32_t* queues, int32_t n_workgroups,
-                        hipStream_t stream);
+                        float scale_log2, int32_t* queues, int32_t cus, hipStream_t stream);
 
 // Device address of the static scratch of psa_attention_fwd_noalloc on the current device
 // (PSA_NOALLOC_SCRATCH_BYTES, 256-byte aligned), looked up once per device.
