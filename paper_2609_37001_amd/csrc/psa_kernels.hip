@@ -1,7 +1,7 @@
 // PSA block-sparse attention forward: HIP kernels for gfx950 (CDNA4, MI355X).
 //
 // Kernels
-//   psa_blockmap_kernel / psa_rowcount_kernel  block map and kept counts (Algorithm 1 per block)
+//   psa_map_kernel                             block map and kept counts (Algorithm 1 per block)
 //   psa_setup_kernel                           stripe parameters and block coordinates -> workspace
 //   psa_count_kernel                           kept key blocks of every (batch, head, query block),
 //                                              and kept-set signatures for the pairing
@@ -60,6 +60,31 @@ __device__ __forceinline__ bool axis_keep(int32_t delta, int32_t width, int32_t 
   const uint32_t ax = (uint32_t)(x < 0 ? -x : x);
   return (ax % (uint32_t)stride) < (uint32_t)width;
 }
+
+// The same test for many distances of one stripe, without a division: x / stride as a multiplication
+// by a 32-bit reciprocal (Granlund and Montgomery, "Division by invariant integers using
+// multiplication"): with 2^(l-1) < stride <= 2^l and mul = ceil(2^(31+l) / stride), the quotient
+// of any x < 2^31 is (x mul) >> (31 + l).
+struct AxisTest {
+  uint32_t mul, shift, stride, width;
+  int32_t offset;
+
+  __device__ __forceinline__ AxisTest(int32_t w, int32_t o, int32_t s) {
+    // A stripe at least as wide as its stride keeps the whole axis.
+    const bool all = w >= s;
+    stride = all ? 0x7fffffffu : (uint32_t)s;               // >= 2
+    width = all ? 0x7fffffffu : (uint32_t)w;
+    offset = all ? 0 : o;
+    const uint32_t l = 32 - __builtin_clz(stride - 1);
+    mul = (uint32_t)(((1ull << (31 + l)) + stride - 1) / stride);
+    shift = l - 1;
+  }
+  __device__ __forceinline__ bool keep(int32_t delta) const {
+    const int32_t x = delta - offset;
+    const uint32_t ax = (uint32_t)(x < 0 ? -x : x);
+    return ax - (__umulhi(ax, mul) >> shift) * stride < width;
+  }
+};
 
 // Coordinates of block b from its first token: frame t and slot s; t = -1 marks a global block
 // (a block holding at least one appended text token).
@@ -164,60 +189,119 @@ __device__ __forceinline__ int2 map_coord(const Geometry& g, int32_t i) {
   return GROUPS ? group_coord(g, i) : block_coord(g, i);
 }
 
-template <bool GROUPS>
-__global__ __launch_bounds__(256) void psa_blockmap_kernel(ParamChunk pc, int32_t head0,
-                                                           Geometry g, uint8_t* __restrict__ map) {
-  const int32_t hc = blockIdx.y;
-  const int64_t pairs = (int64_t)g.nb * g.nb;
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= pairs) return;
-  const int32_t qb = (int32_t)(p / g.nb), kb = (int32_t)(p - (int64_t)qb * g.nb);
-  const bool keep = tile_keep(pc.m[hc], map_coord<GROUPS>(g, qb), map_coord<GROUPS>(g, kb));
-  map[(int64_t)(head0 + hc) * pairs + p] = keep ? 1 : 0;
+__global__ __launch_bounds__(256) void psa_zero_kernel(int64_t* __restrict__ x, int32_t n) {
+  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) x[i] = 0;
 }
 
-// One workgroup per head: per-row counts and the head total (deterministic, no atomics).
-template <bool GROUPS>
-__global__ __launch_bounds__(256) void psa_rowcount_kernel(ParamChunk pc, int32_t head0,
-                                                           Geometry g,
-                                                           int32_t* __restrict__ kept_per_row,
-                                                           int64_t* __restrict__ kept_per_head) {
-  __shared__ int64_t partial[4];
-  const int32_t hc = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Map rows, row counts and head totals in one pass (each output may be null).  A workgroup takes
+// kMapRows rows of one head, a wave kMapRows / 4 of them; a lane decides four consecutive entries of
+// each of its wave's rows at a time and stores them as one word (rows start at any byte).  TABLE:
+// both axes' tests for every distance of the grid are looked up in LDS, filled once per workgroup;
+// without (an axis of more than kMapExtent positions) each is evaluated by multiplication.
+// The map's bytes alone would take 3 us at 40 heads x 591^2 entries (14 MB); what bounds the kernel
+// are the vector and LDS instructions per entry, 22 us with the counts.  One byte, four divisions
+// and two moduli per thread took 63 us, and the counts of one workgroup per head 403 us more.
+constexpr int kMapRows = 16;
+constexpr int kMapExtent = 4096;
+template <bool GROUPS, bool TABLE>
+__global__ __launch_bounds__(256) void psa_map_kernel(ParamChunk pc, int32_t head0, Geometry g,
+                                                      int32_t t_ext, int32_t s_ext,
+                                                      uint8_t* __restrict__ map,
+                                                      int32_t* __restrict__ kept_per_row,
+                                                      unsigned long long* __restrict__ kept_per_head) {
+  constexpr int R = kMapRows / 4;
+  __shared__ uint8_t t_keep[TABLE ? 2 * kMapExtent : 1], s_keep[TABLE ? 2 * kMapExtent : 1];
+  __shared__ int32_t partial[4];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int32_t nb = g.nb, hc = blockIdx.y;
   const psa_stripe_t m = pc.m[hc];
-  int64_t total = 0;
-  for (int32_t qb = wave; qb < g.nb; qb += 4) {
-    const int2 cq = map_coord<GROUPS>(g, qb);
-    int cnt = 0;
-    for (int32_t kb = lane; kb < g.nb; kb += 64)
-      cnt += tile_keep(m, cq, map_coord<GROUPS>(g, kb)) ? 1 : 0;
-    cnt = wave_sum(cnt);
-    if (lane == 0 && kept_per_row) kept_per_row[(int64_t)(head0 + hc) * g.nb + qb] = cnt;
-    total += cnt;
+  const AxisTest ta(m.t_w, m.t_o, m.t_s), sa(m.s_w, m.s_o, m.s_s);
+  if constexpr (TABLE) {
+    for (int32_t i = tid; i < 2 * t_ext - 1; i += 256) t_keep[i] = ta.keep(i - (t_ext - 1));
+    for (int32_t i = tid; i < 2 * s_ext - 1; i += 256) s_keep[i] = sa.keep(i - (s_ext - 1));
+    __syncthreads();
   }
-  if (lane == 0) partial[wave] = total;
-  __syncthreads();
-  if (threadIdx.x == 0 && kept_per_head)
-    kept_per_head[head0 + hc] = partial[0] + partial[1] + partial[2] + partial[3];
+  int2 cq[R];
+  int32_t cnt[R];
+  const int32_t q0 = blockIdx.x * kMapRows + wave * R;
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    cq[r] = map_coord<GROUPS>(g, min(q0 + r, nb - 1));
+    cnt[r] = 0;
+  }
+  for (int32_t k0 = 4 * lane; k0 < nb; k0 += 256) {
+    int2 ck[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) ck[j] = map_coord<GROUPS>(g, min(k0 + j, nb - 1));
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      if (q0 + r >= nb) break;
+      uint32_t word = 0;
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        const int32_t dt = ck[j].x - cq[r].x, ds = ck[j].y - cq[r].y;
+        uint32_t keep;
+        if (cq[r].x < 0 || ck[j].x < 0)
+          keep = 1;
+        else if constexpr (TABLE)
+          keep = t_keep[dt + t_ext - 1] & s_keep[ds + s_ext - 1];
+        else
+          keep = ta.keep(dt) && sa.keep(ds);
+        word |= (k0 + j < nb ? keep : 0u) << (8 * j);
+      }
+      cnt[r] += __builtin_popcount(word);
+      if (map) {
+        uint8_t* dst = map + ((int64_t)(head0 + hc) * nb + q0 + r) * nb + k0;
+        if (k0 + 3 < nb) {
+          __builtin_memcpy(dst, &word, 4);
+        } else {
+          for (int j = 0; k0 + j < nb; j++) dst[j] = (uint8_t)(word >> (8 * j));
+        }
+      }
+    }
+  }
+  int32_t total = 0;
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    cnt[r] = wave_reduce<0>(cnt[r]);
+    if (q0 + r < nb) {
+      total += cnt[r];
+      if (kept_per_row && lane == 0) kept_per_row[(int64_t)(head0 + hc) * nb + q0 + r] = cnt[r];
+    }
+  }
+  if (kept_per_head) {
+    if (lane == 0) partial[wave] = total;
+    __syncthreads();
+    if (tid == 0)
+      atomicAdd(&kept_per_head[head0 + hc],
+                (unsigned long long)((int64_t)partial[0] + partial[1] + partial[2] + partial[3]));
+  }
 }
 
 template <bool GROUPS>
 static hipError_t launch_map(const ParamChunk& pc, int32_t head0, const Geometry& g,
                              uint8_t* blockmap, int32_t* kept_per_row, int64_t* kept_per_head,
                              hipStream_t stream) {
-  if (blockmap) {
-    const int64_t pairs = (int64_t)g.nb * g.nb;
-    dim3 grid((unsigned)((pairs + 255) / 256), (unsigned)pc.n);
-    hipLaunchKernelGGL(psa_blockmap_kernel<GROUPS>, grid, dim3(256), 0, stream, pc, head0, g, blockmap);
-    hipError_t e = hipGetLastError();
+  if (!blockmap && !kept_per_row && !kept_per_head) return hipSuccess;
+  if (kept_per_head) {
+    hipLaunchKernelGGL(psa_zero_kernel, dim3((pc.n + 255) / 256), dim3(256), 0, stream, kept_per_head + head0,
+                       pc.n);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (kept_per_row || kept_per_head) {
-    hipLaunchKernelGGL(psa_rowcount_kernel<GROUPS>, dim3(pc.n), dim3(256), 0, stream, pc, head0, g,
-                       kept_per_row, kept_per_head);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  const int32_t t_ext = GROUPS ? g.tp : g.frames;
+  const int32_t s_ext = GROUPS ? g.hp * g.wp : (g.hw - 1) / g.block + 1;
+  const dim3 grid((unsigned)((g.nb + kMapRows - 1) / kMapRows), (unsigned)pc.n);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, pc, head0, g, t_ext, s_ext, blockmap, kept_per_row,
+                       (unsigned long long*)kept_per_head);
+  };
+  if (t_ext <= kMapExtent && s_ext <= kMapExtent)
+    go(psa_map_kernel<GROUPS, true>);
+  else
+    go(psa_map_kernel<GROUPS, false>);
+  return hipGetLastError();
 }
 
 hipError_t launch_blockmap(const ParamChunk& pc, int32_t head0, const Geometry& g,
