@@ -207,19 +207,16 @@ psa_status_t check_plan_3d(int32_t batch, int32_t n_heads, psa_grid_t grid, psa_
   return check_work(batch, n_heads, workspace, workspace_bytes, g, wl);
 }
 
-// Setup and schedule kernels of a plan over geometry g.
+// The kernels of a plan over geometry g.
 psa_status_t enqueue_plan(int32_t batch, int32_t n_heads, const psa::Geometry& g,
                           const psa_stripe_t* params, void* workspace,
                           const psa::WorkspaceLayout& wl, int32_t* kept_per_row,
                           hipStream_t stream, const char* who) {
-  for (int32_t h0 = 0; h0 < n_heads; h0 += psa::kHeadsPerChunk) {
-    const psa::ParamChunk pc = chunk_of(params, h0, n_heads);
-    hipError_t e = psa::launch_setup(pc, h0, g, workspace, wl, h0 == 0, stream);
-    if (e != hipSuccess) return hip_fail(e, who);
-  }
-  hipError_t e = psa::launch_schedule(g, batch, n_heads, workspace, wl, kept_per_row, stream);
-  if (e != hipSuccess) return hip_fail(e, who);
-  return PSA_OK;
+  psa::ParamChunk chunks[(PSA_MAX_BATCH_HEADS + psa::kHeadsPerChunk - 1) / psa::kHeadsPerChunk];
+  for (int32_t h0 = 0; h0 < n_heads; h0 += psa::kHeadsPerChunk)
+    chunks[h0 / psa::kHeadsPerChunk] = chunk_of(params, h0, n_heads);
+  const hipError_t e = psa::launch_plan(chunks, g, batch, n_heads, workspace, wl, kept_per_row, stream);
+  return e == hipSuccess ? PSA_OK : hip_fail(e, who);
 }
 
 psa_status_t check_layout_args(const void* a, const void* b, int32_t n_bh, int32_t head_dim) {

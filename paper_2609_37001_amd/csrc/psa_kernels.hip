@@ -523,22 +523,6 @@ __global__ __launch_bounds__(256) void psa_tiles3d_kernel(Geometry g, int2* __re
   }
 }
 
-hipError_t launch_setup(const ParamChunk& pc, int32_t head0, const Geometry& g, void* workspace,
-                        const WorkspaceLayout& wl, bool write_coords, hipStream_t stream) {
-  char* ws = (char*)workspace;
-  const bool blocks3d = g.pbt > 0;
-  const bool coords1d = write_coords && !blocks3d;
-  const int32_t n = coords1d ? max(g.nb, pc.n) : pc.n;
-  hipLaunchKernelGGL(psa_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, pc, head0, g,
-                     (PlanHeader*)(ws + wl.header), (psa_stripe_t*)(ws + wl.params),
-                     (int2*)(ws + wl.coords), (int32_t)(write_coords ? (coords1d ? 1 : 2) : 0));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !write_coords || !blocks3d) return e;
-  hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g,
-                     (int2*)(ws + wl.coords), (uint64_t*)(ws + wl.masks));
-  return hipGetLastError();
-}
-
 // A 64-bit mix of a block index (the splitmix64 finalizer); the XOR of the mixes of a kept set
 // is a hash of the set that does not depend on the order of its members.
 __device__ __forceinline__ uint64_t mix64(uint64_t x) {
@@ -762,6 +746,148 @@ __global__ __launch_bounds__(1024) void psa_pairing_kernel(const uint64_t* __res
     if (partner[i] >= -1 && run[i] < pairs_per_head(nb)) dst[run[i]] = make_int2(i, partner[i]);
 }
 
+// Setup, counts, signatures, pairs and pair counts of one head in one workgroup, for sequences of at
+// most kHeadPlanRows blocks (one-dimensional ones, or PSABlock tiles whose coordinates the workspace
+// already holds).  The same pairs as the kernels above, found by comparing every row with every
+// other -- at this size less work than the barriers of a sort.  What bounds the plan of a short
+// sequence is the number of its kernels, 2 to 4 us and more each: 12 heads x 61 blocks took 23 us
+// in four kernels (setup, counts, pairing, pair counts), 11 us in this one.  The work of its one
+// workgroup grows with the square of the rows, though: at 256 blocks it takes 50 us, the four
+// kernels 28, so the line is at 128.
+constexpr int kHeadPlanRows = 128;
+__global__ __launch_bounds__(1024) void psa_head_plan_kernel(
+    ParamChunk pc, int32_t head0, Geometry g, int32_t batch, int32_t n_heads,
+    PlanHeader* __restrict__ header, psa_stripe_t* __restrict__ params, int2* __restrict__ coords,
+    int2* __restrict__ pairs, int32_t* __restrict__ counts, int32_t* __restrict__ kept_per_row) {
+  constexpr int K = kHeadPlanRows / 64;         // blocks per lane
+  constexpr int kTable = 512;                   // axis extents with a table of the distances' tests
+  __shared__ int2 c_of[kHeadPlanRows];
+  __shared__ uint32_t sig[kHeadPlanRows];
+  __shared__ uint64_t key[kHeadPlanRows];       // of the leftover rows, ~0 for the others
+  __shared__ int32_t by_rank[kHeadPlanRows];    // leftover rows in their order
+  __shared__ int2 list[kHeadPlanRows];          // the pairs in the order of their first rows
+  __shared__ uint8_t t_keep[2 * kTable], s_keep[2 * kTable];
+  __shared__ int32_t firsts[K];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int32_t nb = g.nb, np = pairs_per_head(nb), h = head0 + (int32_t)blockIdx.x;
+  const psa_stripe_t m = pc.m[blockIdx.x];
+  const AxisTest ta(m.t_w, m.t_o, m.t_s), sa(m.s_w, m.s_o, m.s_s);
+  const int32_t t_ext = g.pbt > 0 ? g.tp : g.frames;
+  const int32_t s_ext = g.pbt > 0 ? g.hp * g.wp : (g.hw - 1) / g.block + 1;
+  const bool table = t_ext <= kTable && s_ext <= kTable;
+  auto keeps = [&](int2 q, int2 k) {
+    if (q.x == kDeadTile || k.x == kDeadTile) return false;
+    if (q.x < 0 || k.x < 0) return true;
+    if (table) return (t_keep[k.x - q.x + t_ext - 1] & s_keep[k.y - q.y + s_ext - 1]) != 0;
+    return ta.keep(k.x - q.x) && sa.keep(k.y - q.y);
+  };
+  if (tid == 0) {
+    params[h] = m;
+    if (h == 0) header->magic = 0;
+  }
+  if (tid < kHeadPlanRows) {
+    int2 c = make_int2(kDeadTile, 0);
+    if (tid < nb) {
+      c = g.pbt > 0 ? coords[tid] : block_coord(g, tid);
+      if (h == 0 && g.pbt == 0) coords[tid] = c;
+    }
+    c_of[tid] = c;
+    sig[tid] = 0;
+  }
+  if (table) {
+    if (tid < 2 * t_ext - 1) t_keep[tid] = ta.keep(tid - (t_ext - 1));
+    if (tid < 2 * s_ext - 1) s_keep[tid] = sa.keep(tid - (s_ext - 1));
+  }
+  __syncthreads();
+  int2 ck[K];
+  uint32_t mix[K];
+#pragma unroll
+  for (int i = 0; i < K; i++) {
+    ck[i] = c_of[lane + 64 * i];
+    mix[i] = (uint32_t)mix64((uint64_t)(lane + 64 * i));
+  }
+  // Counts and signatures (32 bits of the mix do: a collision costs speed only), a wave per row.
+  for (int32_t q = wave; q < nb; q += 16) {
+    const int2 cq = c_of[q];
+    int32_t cnt = 0;
+    uint32_t x = 0;
+#pragma unroll
+    for (int i = 0; i < K; i++) {
+      if (64 * i >= nb) break;
+      const bool keep = keeps(cq, ck[i]);
+      cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(keep));
+      x ^= keep ? mix[i] : 0u;
+    }
+    for (int off = 32; off > 0; off >>= 1) x ^= __shfl_xor(x, off);
+    if (lane == 0) {
+      sig[q] = x;
+      if (kept_per_row) kept_per_row[(int64_t)h * nb + q] = cnt;
+    }
+  }
+  __syncthreads();
+  // Rows of equal sets pair up in the order of their indices; the last of an odd run is left over.
+  int32_t next = nb;                            // the row this one is the first of a pair with
+  bool first = false, left = false;
+  if (tid < nb) {
+    const uint32_t mine = sig[tid];
+    int32_t before = 0;
+    for (int32_t j = 0; j < nb; j += 4) {       // (rows past the end come after every real one)
+      const uint4 o = *(const uint4*)&sig[j];
+      const uint32_t os[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const bool same = os[u] == mine;
+        before += same && j + u < tid ? 1 : 0;
+        next = min(next, same && j + u > tid ? j + u : nb);
+      }
+    }
+    first = !(before & 1);
+    left = first && next == nb;
+    // Order of the leftover rows: see psa_pairing_kernel.
+    const bool slot_major = m.s_w < m.s_s && (m.t_w >= m.t_s || m.t_w > m.s_w);
+    const int2 c = c_of[tid];
+    uint64_t kk = (uint64_t)tid;
+    if (slot_major)
+      kk |= ((uint64_t)min((uint32_t)c.y, (1u << 26) - 1) << 38) |
+            ((uint64_t)min((uint32_t)c.x, (1u << 25) - 1) << 13);
+    key[tid] = left ? kk : ~0ull;
+    by_rank[tid] = -1;
+  }
+  __syncthreads();
+  int32_t rank = 0;
+  if (left) {
+    const uint64_t mine = key[tid];
+    for (int32_t j = 0; j < nb; j++) rank += key[j] < mine ? 1 : 0;
+    by_rank[rank] = tid;
+    first = !(rank & 1);
+  }
+  const uint64_t starts = __builtin_amdgcn_ballot_w64(first);
+  if (lane == 0 && wave < K) firsts[wave] = __builtin_popcountll(starts);
+  __syncthreads();
+  if (first) {
+    if (left) next = rank + 1 < nb ? by_rank[rank + 1] : -1;
+    int32_t at = __builtin_popcountll(starts & ((1ull << lane) - 1));
+    for (int w = 0; w < wave; w++) at += firsts[w];
+    if (at < np) {
+      list[at] = make_int2(tid, next);
+      pairs[(int64_t)h * np + at] = make_int2(tid, next);
+    }
+  }
+  __syncthreads();
+  // Work of the pairs, a wave per pair.
+  for (int32_t p = wave; p < np; p += 16) {
+    const int2 pr = list[p];
+    const int2 ca = c_of[pr.x], cb = pr.y >= 0 ? c_of[pr.y] : make_int2(kDeadTile, 0);
+    int32_t cnt = 0;
+#pragma unroll
+    for (int i = 0; i < K; i++) {
+      if (64 * i >= nb) break;
+      cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(keeps(ca, ck[i]) || keeps(cb, ck[i])));
+    }
+    for (int32_t b = lane; b < batch; b += 64) counts[((int64_t)b * n_heads + h) * np + p] = cnt;
+  }
+}
+
 // One wave per pair item (batch, head, pair): number of key blocks kept by either row, and the
 // first and last of them that are not global (video blocks; the span the start of the item's
 // stream is placed in).
@@ -812,6 +938,133 @@ constexpr int kLongFactor = 3;
 // Long items are sorted into this many classes of equal width in [0, max work].
 constexpr int kWorkClasses = 64;
 constexpr int kScheduleWaves = 16;
+
+// The schedule of a short list (at most kRankItems items, a few per workgroup): every queue takes a
+// contiguous range of equal work of every (batch, head), as in the schedule below, but lists its
+// items longest first (in kRankClasses classes, by index within one; with 32, 8 and 4 classes the
+// Wan 2.1 1.3B layer takes 1, 2 and 4 % longer).  With few items per workgroup
+// the last ones to be taken set the time: a makespan model of the drawn shapes puts the order by
+// heads at 1.2 to 2 x the ideal with one to three items per workgroup and 1.05 to 1.15 x at six,
+// longest first at 1.1 to 1.45 x and 1.01 to 1.05 x.  Measured: 3 heads of 41774 tokens (1.9 items
+// per workgroup) 1333 -> 982 us, 10 heads of 28875 (4.4) 2204 -> 1910 us; at 12 items per workgroup
+// and more the order by heads is 1 to 4 % faster, because the workgroups of an XCD then read the
+// same key blocks at about the same time.
+// One workgroup; wave w owns items 256 w .. 256 w + 255, 64 at a time.
+constexpr int kRankItems = 4096;
+constexpr int kRankClasses = 64;
+__global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restrict__ counts,
+                                                        int32_t* __restrict__ order,
+                                                        int32_t* __restrict__ queues,
+                                                        int32_t* __restrict__ starts,
+                                                        PlanHeader* __restrict__ header,
+                                                        PlanHeader done, int32_t per_head) {
+  constexpr int C = kRankItems / 1024, kBins = kNumQueues * kRankClasses;
+  static_assert(kBins <= 1024, "a thread per bin");
+  __shared__ int32_t hist[16][kBins];
+  __shared__ int32_t head_at[PSA_MAX_BATCH_HEADS + 1];    // work before each (batch, head)
+  __shared__ int32_t part[16], part_max[16], bin_part[16];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int32_t n = done.n_bh * per_head;
+  for (int32_t i = tid; i < 16 * kBins; i += 1024) (&hist[0][0])[i] = 0;
+  int32_t cnt[C], at[C], bh[C], sum = 0, mx = 0;
+#pragma unroll
+  for (int c = 0; c < C; c++) {
+    const int32_t i = 256 * wave + 64 * c + lane;
+    cnt[c] = i < n ? counts[i] : -kItemOverhead;
+    bh[c] = i / per_head;
+  }
+#pragma unroll
+  for (int c = 0; c < C; c++) {
+    const int32_t w = cnt[c] + kItemOverhead;
+    const int32_t incl = wave_incl_sum(w, lane);
+    at[c] = sum + incl - w;                               // work before the item within the wave
+    sum += __builtin_amdgcn_readlane(incl, 63);
+    mx = max(mx, cnt[c]);
+  }
+  mx = wave_reduce<2>(mx);
+  if (lane == 0) {
+    part[wave] = sum;
+    part_max[wave] = mx;
+  }
+  __syncthreads();
+  int32_t before = 0, total = 0;
+  for (int w = 0; w < 16; w++) {
+    before += w < wave ? part[w] : 0;
+    total += part[w];
+    mx = max(mx, part_max[w]);
+  }
+#pragma unroll
+  for (int c = 0; c < C; c++) {
+    const int32_t i = 256 * wave + 64 * c + lane;
+    at[c] += before;
+    if (i < n && i == bh[c] * per_head) head_at[bh[c]] = at[c];
+  }
+  if (tid == 0) head_at[done.n_bh] = total;
+  __syncthreads();
+  int32_t bin[C];
+#pragma unroll
+  for (int c = 0; c < C; c++) {
+    const int32_t i = 256 * wave + 64 * c + lane;
+    bin[c] = 0;
+    if (i < n) {
+      // The (batch, head)s start on different queues: one of fewer than kNumQueues items does not
+      // fill them all.
+      const uint32_t h0 = head_at[bh[c]], head = head_at[bh[c] + 1] - h0;
+      const uint32_t range = (uint32_t)(((uint64_t)(at[c] - h0) * kNumQueues) / head);
+      const int32_t cls = (int32_t)((uint32_t)cnt[c] * kRankClasses / (uint32_t)(mx + 1));
+      bin[c] = (int32_t)((range + bh[c]) % kNumQueues) * kRankClasses + kRankClasses - 1 - cls;
+      atomicAdd(&hist[wave][bin[c]], 1);
+    }
+  }
+  __syncthreads();
+  // Positions: an exclusive sum over (bin, wave).
+  int32_t col = 0, incl = 0;
+  if (tid < kBins) {
+    for (int w = 0; w < 16; w++) col += hist[w][tid];
+    incl = wave_incl_sum(col, lane);
+    if (lane == 63) bin_part[wave] = incl;
+  }
+  __syncthreads();
+  if (tid < kBins) {
+    int32_t pos = incl - col;
+    for (int w = 0; w < wave; w++) pos += bin_part[w];
+    if (tid % kRankClasses == 0) queues[tid / kRankClasses] = pos;
+    if (tid == 0) queues[kNumQueues] = n;
+    for (int w = 0; w < 16; w++) {
+      const int32_t x = hist[w][tid];
+      hist[w][tid] = pos;
+      pos += x;
+    }
+  }
+  if (tid < kNumQueues) queues[kQueueCounters + tid * kCounterStride] = 0;
+  __syncthreads();
+  // Stable scatter: the lanes of 64 items that share a bin are found with one ballot per bit.
+#pragma unroll
+  for (int c = 0; c < C; c++) {
+    const int32_t i = 256 * wave + 64 * c + lane;
+    const bool valid = i < n;
+    uint64_t same = __builtin_amdgcn_ballot_w64(valid);
+    if (!same) break;
+#pragma unroll
+    for (int bit = 1; bit < kBins; bit <<= 1) {
+      const uint64_t ones = __builtin_amdgcn_ballot_w64(valid && (bin[c] & bit));
+      same &= (bin[c] & bit) ? ones : ~ones;
+    }
+    const int32_t base = valid ? hist[wave][bin[c]] : 0;
+    __builtin_amdgcn_wave_barrier();
+    if (valid) {
+      order[base + __builtin_popcountll(same & ((1ull << lane) - 1))] = i;
+      if (starts) starts[i] = 0;                          // streams ascend from their first block
+      if (__builtin_ctzll(same) == lane) hist[wave][bin[c]] = base + __builtin_popcountll(same);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  if (tid == 0) {
+    __threadfence();
+    *header = done;
+  }
+}
 
 // Single workgroup.  Every queue x (the XCD of the workgroups that start on it) begins with its
 // share of the long items, longest first and dealt round-robin over the queues.  The other items
@@ -1273,37 +1526,78 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
 static bool has_starts(const Geometry& g) { return g.block == 128; }
 
-hipError_t launch_schedule(const Geometry& g, int32_t batch, int32_t n_heads, void* workspace,
-                           const WorkspaceLayout& wl, int32_t* kept_per_row, hipStream_t stream) {
+// Whether the items are few enough to be listed longest first: at most eight per CU and workgroup
+// of head dim 128 (see psa_rank_kernel).
+static bool ranked(const Geometry& g, int32_t n_items) { return n_items <= kRankItems * 64 / g.block; }
+
+// Whether one kernel per head makes the whole plan but the order.
+static bool head_planned(const Geometry& g) { return g.nb <= kHeadPlanRows; }
+
+hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batch, int32_t n_heads,
+                       void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
+                       hipStream_t stream) {
   char* ws = (char*)workspace;
-  const psa_stripe_t* params = (const psa_stripe_t*)(ws + wl.params);
-  const int2* coords = (const int2*)(ws + wl.coords);
+  PlanHeader* header = (PlanHeader*)(ws + wl.header);
+  psa_stripe_t* params = (psa_stripe_t*)(ws + wl.params);
+  int2* coords = (int2*)(ws + wl.coords);
+  int2* pairs = (int2*)(ws + wl.pairs);
   int32_t* counts = (int32_t*)(ws + wl.counts);
-  hipError_t e;
-  // Row counts and kept-set signatures of one batch element, the pairs of each head, then the
-  // work of every pair item.
-  const int32_t n_rows = n_heads * g.nb;
-  hipLaunchKernelGGL(psa_count_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, stream, params, coords,
-                     kept_per_row, (uint64_t*)(ws + wl.sigs), n_rows, g.nb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(psa_pairing_kernel, dim3(n_heads), dim3(1024), 0, stream,
-                     (const uint64_t*)(ws + wl.sigs), params, coords, (int2*)(ws + wl.pairs), g.nb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int32_t per_head = pairs_per_head(g.nb), n_items = batch * n_heads * per_head;
-  hipLaunchKernelGGL(psa_paircount_kernel, dim3((n_items + 3) / 4), dim3(256), 0, stream, params, coords,
-                     (const int2*)(ws + wl.pairs), counts, (uint32_t*)(ws + wl.spans), n_items, n_heads,
+  const int32_t n_chunks = (n_heads + kHeadsPerChunk - 1) / kHeadsPerChunk;
+  const bool blocks3d = g.pbt > 0, fused = head_planned(g) && ranked(g, n_items);
+  hipError_t e;
+  if (blocks3d) {
+    hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
+                       (uint64_t*)(ws + wl.masks));
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  for (int32_t c = 0; c < n_chunks; c++) {
+    const ParamChunk& pc = chunks[c];
+    const int32_t head0 = c * kHeadsPerChunk;
+    if (fused) {
+      hipLaunchKernelGGL(psa_head_plan_kernel, dim3(pc.n), dim3(1024), 0, stream, pc, head0, g, batch, n_heads,
+                         header, params, coords, pairs, counts, kept_per_row);
+    } else {
+      const int32_t n = c == 0 && !blocks3d ? max(g.nb, pc.n) : pc.n;
+      hipLaunchKernelGGL(psa_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, pc, head0, g, header,
+                         params, coords, (int32_t)(c == 0 ? (blocks3d ? 2 : 1) : 0));
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (!fused) {
+    // Row counts and kept-set signatures of one batch element, the pairs of each head, then the
+    // work of every pair item.
+    const int32_t n_rows = n_heads * g.nb;
+    hipLaunchKernelGGL(psa_count_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, stream,
+                       (const psa_stripe_t*)params, (const int2*)coords, kept_per_row,
+                       (uint64_t*)(ws + wl.sigs), n_rows, g.nb);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(psa_pairing_kernel, dim3(n_heads), dim3(1024), 0, stream,
+                       (const uint64_t*)(ws + wl.sigs), (const psa_stripe_t*)params, (const int2*)coords, pairs,
+                       g.nb);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(psa_paircount_kernel, dim3((n_items + 3) / 4), dim3(256), 0, stream,
+                       (const psa_stripe_t*)params, (const int2*)coords, (const int2*)pairs, counts,
+                       (uint32_t*)(ws + wl.spans), n_items, n_heads, g.nb);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  int32_t* order = (int32_t*)(ws + wl.order);
+  int32_t* queues = (int32_t*)(ws + wl.queues);
+  int32_t* starts = has_starts(g) ? (int32_t*)(ws + wl.starts) : nullptr;
+  const PlanHeader done = plan_header(g, batch, n_heads);
+  if (ranked(g, n_items)) {
+    hipLaunchKernelGGL(psa_rank_kernel, dim3(1), dim3(1024), 0, stream, (const int32_t*)counts, order, queues,
+                       starts, header, done, per_head);
+    return hipGetLastError();
+  }
+  const uint32_t* spans = starts ? (const uint32_t*)(ws + wl.spans) : nullptr;
+  uint32_t* runspans = starts ? (uint32_t*)(ws + wl.runspans) : nullptr;
+  hipLaunchKernelGGL(psa_schedule_kernel, dim3(1), dim3(1024), 0, stream, (const int32_t*)counts, order, queues,
+                     header, done, per_head, (int32_t)!starts, spans, runspans);
+  if ((e = hipGetLastError()) != hipSuccess || !starts) return e;
+  hipLaunchKernelGGL(psa_starts_kernel, dim3(kNumQueues), dim3(1024), 0, stream, (const int32_t*)counts, spans,
+                     (const uint32_t*)runspans, (const int32_t*)order, queues, starts, header, done, per_head,
                      g.nb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(psa_schedule_kernel, dim3(1), dim3(1024), 0, stream, (const int32_t*)counts,
-                     (int32_t*)(ws + wl.order), (int32_t*)(ws + wl.queues), (PlanHeader*)(ws + wl.header),
-                     plan_header(g, batch, n_heads), per_head, (int32_t)!has_starts(g),
-                     has_starts(g) ? (const uint32_t*)(ws + wl.spans) : nullptr,
-                     has_starts(g) ? (uint32_t*)(ws + wl.runspans) : nullptr);
-  if ((e = hipGetLastError()) != hipSuccess || !has_starts(g)) return e;
-  hipLaunchKernelGGL(psa_starts_kernel, dim3(kNumQueues), dim3(1024), 0, stream, (const int32_t*)counts,
-                     (const uint32_t*)(ws + wl.spans), (const uint32_t*)(ws + wl.runspans),
-                     (const int32_t*)(ws + wl.order), (int32_t*)(ws + wl.queues), (int32_t*)(ws + wl.starts),
-                     (PlanHeader*)(ws + wl.header), plan_header(g, batch, n_heads), per_head, g.nb);
   return hipGetLastError();
 }
 

@@ -100,9 +100,6 @@ hipError_t launch_blockmap(const ParamChunk& pc, int32_t head0, const Geometry& 
                            uint8_t* blockmap, int32_t* kept_per_row, int64_t* kept_per_head,
                            hipStream_t stream);
 
-hipError_t launch_setup(const ParamChunk& pc, int32_t head0, const Geometry& g, void* workspace,
-                        const WorkspaceLayout& wl, bool write_coords, hipStream_t stream);
-
 // PSABlock-level block map: groups 0 .. T'H'W'-1 are the PSABlocks, group T'H'W' (with text)
 // the text; g.nb must be the group count.
 hipError_t launch_group_blockmap(const ParamChunk& pc, int32_t head0, const Geometry& g,
@@ -121,9 +118,11 @@ hipError_t launch_l2(const void* o, const void* ref, int32_t n_bh, int64_t elems
 hipError_t launch_layout(const void* src, void* dst, int32_t n_bh, int32_t head_dim,
                          const Geometry& g, bool to_blocks, hipStream_t stream);
 
-// Counts the kept blocks of every work item, orders them, and writes the header last.
-hipError_t launch_schedule(const Geometry& g, int32_t batch, int32_t n_heads, void* workspace,
-                           const WorkspaceLayout& wl, int32_t* kept_per_row, hipStream_t stream);
+// The plan: stripe parameters (chunks of kHeadsPerChunk heads) and block coordinates, the pairs of
+// query blocks, their work and their order; the header last.
+hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batch, int32_t n_heads,
+                       void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
+                       hipStream_t stream);
 
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
                          int32_t batch, int32_t n_heads, int32_t head_dim, const Geometry& g,

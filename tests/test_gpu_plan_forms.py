@@ -1,0 +1,62 @@
+"""Every query row of a plan is computed exactly once and over its own keys, at the sizes where the
+plan changes its kernels: 128 | 129 blocks (one kernel per head | several), 64 | 65 heads (one block
+of parameters | two), 4096 | 4160 items at block 64 and 2048 | 2080 at block 128 (listed longest
+first | by heads), fewer items than queues, all-equal and all-different rows, batch 2.
+
+With q = 0 every kept key has weight 1, so the normaliser is the logarithm of the number of kept keys
+and o is the mean of v; outputs start as NaN."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2609_37001_amd as psa
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+INF = 0x7FFFFFFF
+
+
+def stripes(heads, f, sp, seed):
+    rng = np.random.default_rng([13, seed])
+    out = [(f, 0, INF, sp, 0, INF), (1, 0, INF, 1, 0, INF), (1, f + 3, INF, 1, 0, INF)]   # all, diagonal, none
+    while len(out) < heads:
+        out.append((int(rng.integers(1, f + 1)), int(rng.integers(-2, 3)), int(rng.choice([1, 2, 3, INF])),
+                    int(rng.integers(1, sp + 1)), int(rng.integers(-1, 2)), int(rng.choice([1, 3, 5, 6, INF]))))
+    return out[:heads]
+
+
+# batch, heads, (F, H, W, text), block, head_dim
+CASES = [(1, 1, (1, 1, 7, 0), 64, 64), (2, 3, (1, 8, 16, 0), 128, 128), (1, 3, (2, 8, 16, 5), 128, 64),
+         (1, 4, (16, 8, 128, 0), 128, 128), (1, 4, (16, 8, 128, 1), 128, 128), (2, 4, (16, 8, 64, 0), 64, 128),
+         (1, 64, (3, 8, 24, 3), 64, 64), (2, 65, (3, 8, 24, 3), 64, 64), (1, 65, (3, 4, 11, 0), 128, 128),
+         (1, 64, (16, 8, 64, 0), 64, 64), (1, 65, (16, 8, 64, 0), 64, 64),
+         (2, 32, (8, 8, 128, 0), 128, 64), (2, 33, (8, 8, 128, 0), 128, 64), (1, 16, (32, 8, 128, 0), 128, 128)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_every_row_once(case):
+    batch, heads, grid, block, d = case
+    f, h, w, nt = grid
+    t = gu.torch()
+    n = f * h * w + nt
+    params = stripes(heads, f, -(-(h * w) // block), heads)
+    gen = t.Generator(device="cuda").manual_seed(5)
+    k = t.randn((batch, heads, n, d), generator=gen, device="cuda", dtype=t.bfloat16)
+    v = t.full_like(k, 0.5)
+    q = t.zeros_like(k)
+    o = t.full_like(k, float("nan"))
+    o, lse, kept = psa.attention_fwd(q, k, v, grid, block, params, out=o, return_lse=True, return_kept_per_row=True)
+    t.cuda.synchronize()
+    keep = oracle.blockmap(params, f, h, w, nt, block).astype(bool)
+    assert np.array_equal(kept.cpu().numpy(), keep.sum(2))
+    size = np.minimum(block, n - block * np.arange(keep.shape[1]))
+    keys = np.repeat(keep @ size, size, axis=1)                          # [heads, n]
+    with np.errstate(divide="ignore"):
+        want = np.log(keys)
+    got = lse.cpu().numpy()
+    # sums of up to 2^24 ones are exact in fp32; ln 2 x log2 in fp32 is within 2^-21 of ln here
+    assert np.array_equal(np.isneginf(got), np.broadcast_to(keys == 0, got.shape))
+    fin = np.broadcast_to(keys > 0, got.shape)
+    assert np.abs(got[fin] - np.broadcast_to(want, got.shape)[fin]).max() <= 2e-5
+    assert t.equal(o, t.from_numpy(np.where(keys > 0, 0.5, 0.0)).to(o)[None, :, :, None].expand_as(o))
