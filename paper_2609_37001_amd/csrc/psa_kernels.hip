@@ -939,7 +939,7 @@ constexpr int kLongFactor = 3;
 constexpr int kWorkClasses = 64;
 constexpr int kScheduleWaves = 16;
 
-// The schedule of a short list (at most kRankItems items, a few per workgroup): every queue takes a
+// The schedule of a short list: every queue takes a
 // contiguous range of equal work of every (batch, head), as in the schedule below, but lists its
 // items longest first (in kRankClasses classes, by index within one; with 32, 8 and 4 classes the
 // Wan 2.1 1.3B layer takes 1, 2 and 4 % longer).  With few items per workgroup
@@ -949,8 +949,8 @@ constexpr int kScheduleWaves = 16;
 // per workgroup) 1333 -> 982 us, 10 heads of 28875 (4.4) 2204 -> 1910 us; at 12 items per workgroup
 // and more the order by heads is 1 to 4 % faster, because the workgroups of an XCD then read the
 // same key blocks at about the same time.
-// One workgroup; wave w owns items 256 w .. 256 w + 255, 64 at a time.
-constexpr int kRankItems = 4096;
+// One workgroup; a wave owns a contiguous slice of the items, 64 cw of them, 64 at a time.
+constexpr int kRankItems = 16384;
 constexpr int kRankClasses = 64;
 __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restrict__ counts,
                                                         int32_t* __restrict__ order,
@@ -964,17 +964,19 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   __shared__ int32_t head_at[PSA_MAX_BATCH_HEADS + 1];    // work before each (batch, head)
   __shared__ int32_t part[16], part_max[16], bin_part[16];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int32_t n = done.n_bh * per_head;
+  const int32_t n = done.n_bh * per_head, cw = (n + 1023) / 1024;
   for (int32_t i = tid; i < 16 * kBins; i += 1024) (&hist[0][0])[i] = 0;
   int32_t cnt[C], at[C], bh[C], sum = 0, mx = 0;
 #pragma unroll
   for (int c = 0; c < C; c++) {
-    const int32_t i = 256 * wave + 64 * c + lane;
+    if (c >= cw) continue;
+    const int32_t i = 64 * (cw * wave + c) + lane;
     cnt[c] = i < n ? counts[i] : -kItemOverhead;
     bh[c] = i / per_head;
   }
 #pragma unroll
   for (int c = 0; c < C; c++) {
+    if (c >= cw) continue;
     const int32_t w = cnt[c] + kItemOverhead;
     const int32_t incl = wave_incl_sum(w, lane);
     at[c] = sum + incl - w;                               // work before the item within the wave
@@ -995,7 +997,8 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   }
 #pragma unroll
   for (int c = 0; c < C; c++) {
-    const int32_t i = 256 * wave + 64 * c + lane;
+    if (c >= cw) continue;
+    const int32_t i = 64 * (cw * wave + c) + lane;
     at[c] += before;
     if (i < n && i == bh[c] * per_head) head_at[bh[c]] = at[c];
   }
@@ -1004,7 +1007,8 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   int32_t bin[C];
 #pragma unroll
   for (int c = 0; c < C; c++) {
-    const int32_t i = 256 * wave + 64 * c + lane;
+    if (c >= cw) continue;
+    const int32_t i = 64 * (cw * wave + c) + lane;
     bin[c] = 0;
     if (i < n) {
       // The (batch, head)s start on different queues: one of fewer than kNumQueues items does not
@@ -1041,7 +1045,8 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   // Stable scatter: the lanes of 64 items that share a bin are found with one ballot per bit.
 #pragma unroll
   for (int c = 0; c < C; c++) {
-    const int32_t i = 256 * wave + 64 * c + lane;
+    if (c >= cw) continue;
+    const int32_t i = 64 * (cw * wave + c) + lane;
     const bool valid = i < n;
     uint64_t same = __builtin_amdgcn_ballot_w64(valid);
     if (!same) break;
@@ -1526,9 +1531,12 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
 static bool has_starts(const Geometry& g) { return g.block == 128; }
 
-// Whether the items are few enough to be listed longest first: at most eight per CU and workgroup
-// of head dim 128 (see psa_rank_kernel).
-static bool ranked(const Geometry& g, int32_t n_items) { return n_items <= kRankItems * 64 / g.block; }
+// Whether the items are listed longest first (psa_rank_kernel).  Block 128: up to eight per CU; from
+// there to 32 per CU the order by heads and this one differ by -1.5 to +1.5 %, beyond it is up to 4 %
+// faster (K/V blocks shared in the L2).  Block 64: as long as the kernel can hold the list; 4096 to
+// 8192 items gain 1.5 to 12 % (the schedule kernel takes 35 to 45 us there, this one 10), 8192 to
+// 16384 0.4 to 7.5 %.
+static bool ranked(const Geometry& g, int32_t n_items) { return n_items <= (g.block == 64 ? kRankItems : 2048); }
 
 // Whether one kernel per head makes the whole plan but the order.
 static bool head_planned(const Geometry& g) { return g.nb <= kHeadPlanRows; }
