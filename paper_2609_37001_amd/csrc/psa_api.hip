@@ -483,7 +483,7 @@ psa_status_t psa_dense_fwd(const void* q, const void* k, const void* v, void* o,
   if (((uintptr_t)workspace & 255) != 0)
     return fail(PSA_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   const float c = softmax_scale * 1.4426950408889634f;
-  hipError_t e = psa::launch_dense(q, k, v, o, lse, batch, n_heads, head_dim, n_tokens, c,
+  hipError_t e = psa::launch_dense(q, k, v, o, lse, batch, n_heads, head_dim, n_tokens, block, c,
                                    (int32_t*)workspace, compute_units(), stream);
   if (e != hipSuccess) return hip_fail(e, "psa_dense_fwd kernel launch");
   return PSA_OK;

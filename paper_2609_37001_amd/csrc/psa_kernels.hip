@@ -493,14 +493,21 @@ WorkspaceLayout workspace_layout(int32_t batch, int32_t n_heads, int32_t nb, boo
 
 // Copies one chunk of stripe parameters into the workspace; the first chunk also invalidates
 // the plan header (write_coords != 0) and writes the block coordinate table of one-dimensional
-// blocks (write_coords == 1; 3D tiles get theirs from psa_tiles3d_kernel).
+// blocks (write_coords == 1; 3D tiles get theirs from psa_tiles3d_kernel).  write_header: the plan
+// has no other kernel after this one.
 __global__ __launch_bounds__(256) void psa_setup_kernel(ParamChunk pc, int32_t head0, Geometry g,
                                                         PlanHeader* __restrict__ header,
                                                         psa_stripe_t* __restrict__ params,
                                                         int2* __restrict__ coords,
-                                                        int32_t write_coords) {
+                                                        int32_t write_coords, PlanHeader done,
+                                                        int32_t write_header) {
   const int32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (write_coords && i == 0) header->magic = 0;
+  if (i == 0) {
+    if (write_header)
+      *header = done;
+    else if (write_coords)
+      header->magic = 0;
+  }
   if (i < pc.n) params[head0 + i] = pc.m[i];
   if (write_coords == 1 && i < g.nb) coords[i] = block_coord(g, i);
 }
@@ -533,12 +540,14 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
 }
 
 // One wave per (head, query block): the number of kept key blocks (kept_per_row, if asked) and the
-// signature of the kept set.
+// signature of the kept set (sigs, if asked).  With a header, this is the plan's last kernel.
 __global__ __launch_bounds__(256) void psa_count_kernel(const psa_stripe_t* __restrict__ params,
                                                         const int2* __restrict__ coords,
                                                         int32_t* __restrict__ kept_per_row,
                                                         uint64_t* __restrict__ sigs, int32_t n_rows,
-                                                        int32_t nb) {
+                                                        int32_t nb, PlanHeader* __restrict__ header,
+                                                        PlanHeader done) {
+  if (header && blockIdx.x == 0 && threadIdx.x == 0) *header = done;
   const int32_t row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= n_rows) return;
   const int32_t h = row / nb, qb = row - h * nb;
@@ -555,7 +564,7 @@ __global__ __launch_bounds__(256) void psa_count_kernel(const psa_stripe_t* __re
   for (int off = 32; off > 0; off >>= 1) sig ^= __shfl_xor(sig, off);
   if (lane == 0) {
     if (kept_per_row) kept_per_row[row] = cnt;
-    sigs[row] = sig;
+    if (sigs) sigs[row] = sig;
   }
 }
 
@@ -1528,6 +1537,13 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   return h;
 }
 
+// Whether this many query blocks run on the split engine: at most one workgroup per CU at block
+// 128 and two of the half as large ones at block 64, on the 256 CUs of an MI355X (a fixed number:
+// the plan and every later run have to agree, and the sparse and the dense path round alike).
+static bool split_rows(int32_t n_bh, int32_t nb, int32_t block) {
+  return (int64_t)n_bh * nb <= 256 * (128 / block);
+}
+
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
 static bool has_starts(const Geometry& g) { return g.block == 128; }
 
@@ -1553,6 +1569,8 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const int32_t per_head = pairs_per_head(g.nb), n_items = batch * n_heads * per_head;
   const int32_t n_chunks = (n_heads + kHeadsPerChunk - 1) / kHeadsPerChunk;
   const bool blocks3d = g.pbt > 0, fused = head_planned(g) && ranked(g, n_items);
+  const bool split = split_rows(batch * n_heads, g.nb, g.block);
+  const PlanHeader done = plan_header(g, batch, n_heads);
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -1562,15 +1580,25 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   for (int32_t c = 0; c < n_chunks; c++) {
     const ParamChunk& pc = chunks[c];
     const int32_t head0 = c * kHeadsPerChunk;
-    if (fused) {
+    if (fused && !split) {
       hipLaunchKernelGGL(psa_head_plan_kernel, dim3(pc.n), dim3(1024), 0, stream, pc, head0, g, batch, n_heads,
                          header, params, coords, pairs, counts, kept_per_row);
     } else {
       const int32_t n = c == 0 && !blocks3d ? max(g.nb, pc.n) : pc.n;
       hipLaunchKernelGGL(psa_setup_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, pc, head0, g, header,
-                         params, coords, (int32_t)(c == 0 ? (blocks3d ? 2 : 1) : 0));
+                         params, coords, (int32_t)(c == 0 ? (blocks3d ? 2 : 1) : 0),
+                         done, (int32_t)(split && !kept_per_row && c == n_chunks - 1));
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (split) {
+    // The split engine needs the parameters and coordinates only.
+    if (!kept_per_row) return hipSuccess;
+    const int32_t n_rows = n_heads * g.nb;
+    hipLaunchKernelGGL(psa_count_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, stream,
+                       (const psa_stripe_t*)params, (const int2*)coords, kept_per_row, nullptr, n_rows, g.nb,
+                       header, done);
+    return hipGetLastError();
   }
   if (!fused) {
     // Row counts and kept-set signatures of one batch element, the pairs of each head, then the
@@ -1578,7 +1606,7 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
     const int32_t n_rows = n_heads * g.nb;
     hipLaunchKernelGGL(psa_count_kernel, dim3((n_rows + 3) / 4), dim3(256), 0, stream,
                        (const psa_stripe_t*)params, (const int2*)coords, kept_per_row,
-                       (uint64_t*)(ws + wl.sigs), n_rows, g.nb);
+                       (uint64_t*)(ws + wl.sigs), n_rows, g.nb, nullptr, done);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(psa_pairing_kernel, dim3(n_heads), dim3(1024), 0, stream,
                        (const uint64_t*)(ws + wl.sigs), (const psa_stripe_t*)params, (const int2*)coords, pairs,
@@ -1592,7 +1620,6 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   int32_t* order = (int32_t*)(ws + wl.order);
   int32_t* queues = (int32_t*)(ws + wl.queues);
   int32_t* starts = has_starts(g) ? (int32_t*)(ws + wl.starts) : nullptr;
-  const PlanHeader done = plan_header(g, batch, n_heads);
   if (ranked(g, n_items)) {
     hipLaunchKernelGGL(psa_rank_kernel, dim3(1), dim3(1024), 0, stream, (const int32_t*)counts, order, queues,
                        starts, header, done, per_head);
@@ -1719,23 +1746,23 @@ struct WaveState {
   float l;             // running sum of the bf16-rounded P over this lane's keys
 };
 
-// A key/value block is processed in steps of HK = 64 keys (S^T: HK/32 groups of 32 keys per
-// wave): two halves at block 128, the whole block at block 64.  Every step updates the
-// online-softmax statistics on its own.
-template <int D, int BLK>
+// A key/value block is processed in steps of HK_ keys (S^T: HK_/32 groups of 32 keys per wave): 64 in
+// the pair engine (two halves at block 128, the whole block at block 64), half a block in the split
+// engine.  Every step updates the online-softmax statistics on its own.
+template <int D, int BLK, int HK_ = 64>
 struct Half {
-  static constexpr int HK = 64;               // keys per step
+  static constexpr int HK = HK_;              // keys per step
   static constexpr int KT = HK / 32;          // 32-key groups of S^T per half
   static constexpr int KC = HK / 16;          // 16-key chunks per half
 };
 
 // S^T = K Q^T for keys [k0, k0 + HK) of the block (K rows from LDS).
-template <int D, int BLK>
+template <int D, int BLK, int HK = 64>
 __device__ __forceinline__ void qk_half(const WaveState<D, BLK>& st,
-                                        f32x16 (&s)[Half<D, BLK>::KT], const uint8_t* sk, int k0,
+                                        f32x16 (&s)[Half<D, BLK, HK>::KT], const uint8_t* sk, int k0,
                                         int lane) {
   using T = Tile<D, BLK>;
-  using H = Half<D, BLK>;
+  using H = Half<D, BLK, HK>;
   const int h = lane >> 5;
   const int krow0 = k0 + key_perm(lane & 31);
   const int ksw = swz<T::CPR>(krow0);   // identical for krow0 + 32 kt
@@ -1769,13 +1796,13 @@ __device__ __forceinline__ void qk_half(const WaveState<D, BLK>& st,
 //  * Masked keys: past the sequence end (one-dimensional blocks: only the last block), or, in
 //    the PSABlock-centric layout (PAD), every position whose bit in the tile's validity words
 //    (lo: positions 0..63, hi: 64..127) is clear -- 3D padding and the end of the sequence.
-template <int D, int BLK, bool PAD>
+template <int D, int BLK, bool PAD, int HK = 64>
 __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
-                                                f32x16 (&s)[Half<D, BLK>::KT], const uint8_t* sv,
+                                                f32x16 (&s)[Half<D, BLK, HK>::KT], const uint8_t* sv,
                                                 int kb, int k0, int n, bool tail, uint64_t lo,
                                                 uint64_t hi, int lane, int& fresh) {
   using T = Tile<D, BLK>;
-  using H = Half<D, BLK>;
+  using H = Half<D, BLK, HK>;
   const int h = lane >> 5, g = lane >> 4, j16 = lane & 15;
   if (tail) {
     asm volatile("" ::: "memory");        // keep the mask a branch taken only by partial tiles
@@ -2424,6 +2451,167 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Split engine: for problems of so few query blocks that the pair engine's items leave CUs idle.  A
+// workgroup of the pair engine's shape takes ONE query block; its two groups of waves hold the same
+// rows and take half of every key block each (64 keys at block 128, 32 at block 64), and the two
+// online-softmax states are merged through LDS at the end.  One workgroup per query block, all
+// resident at once, so nothing is scheduled: the time is that of the longest query block, half of
+// what it is as half of a pair.  It needs no pairs and no order from the plan.
+// Measured (plan and attention, before the pair engine's plan): 2 heads x 1024 x 64, block 64 35 us ->
+// 28; 2 heads x 4672 x 128, block 128 79 -> 42; 18 dense heads of 1116 x 64 24 -> 17; 1.5 times over
+// 24 drawn calls of this size.
+// ---------------------------------------------------------------------------------------------
+
+// Key blocks of the longest sequence the split engine takes.
+constexpr int kSplitBlocks = 512;
+
+template <int D, int BLK, bool SPARSE, bool PAD>
+__global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2))) void psa_split_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
+    __bf16* __restrict__ o, float* __restrict__ lse, const uint8_t* __restrict__ ws, PlanView pv,
+    PlanHeader expect, float c) {
+  using T = Tile<D, BLK>;
+  constexpr int HK = BLK / 2, W = 2 * T::kWaves, DH = T::DT / 2;
+  using H = Half<D, BLK, HK>;
+  __shared__ __attribute__((aligned(1024))) uint8_t sk[2][T::BYTES];
+  __shared__ __attribute__((aligned(1024))) uint8_t sv[2][T::BYTES];
+  __shared__ uint16_t list[SPARSE ? kSplitBlocks : 1];
+  __shared__ int32_t found[W];
+  __shared__ float2 stat[W][32];              // (m, l) of every wave's rows
+
+  if constexpr (SPARSE) {
+    // A workspace without a finished plan for exactly these sizes is left alone.
+    if (!plan_matches(*(const PlanHeader*)ws, expect)) return;
+  }
+  const int32_t n_heads = expect.n_heads, n = expect.n, nb = expect.nb;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, gw = wave & (T::kWaves - 1);
+  const int grp = __builtin_amdgcn_readfirstlane(wave / T::kWaves);
+  const int h = lane >> 5, r32 = lane & 31;
+  const int32_t bh = blockIdx.x / nb, qb = blockIdx.x - bh * nb;
+  const size_t off = (size_t)bh * n * D;
+  const __bf16 *kh = k + off, *vh = v + off;
+  const int row = qb * BLK + gw * 32 + r32;
+
+  // The kept key blocks, ascending.
+  int32_t nu = nb;
+  if constexpr (SPARSE) {
+    const psa_stripe_t m = ((const psa_stripe_t*)(ws + pv.params))[bh % n_heads];
+    const int2* coords = (const int2*)(ws + pv.coords);
+    const int2 cq = coords[qb];
+    nu = 0;
+    for (int32_t base = 0; base < nb; base += W * 64) {
+      const int32_t kb = base + tid;
+      const bool keep = kb < nb && tile_keep(m, cq, coords[kb]);
+      const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+      if (lane == 0) found[wave] = __builtin_popcountll(mask);
+      __syncthreads();
+      int32_t pos = nu;
+#pragma unroll
+      for (int w = 0; w < W; w++) {
+        pos += w < wave ? found[w] : 0;
+        nu += found[w];
+      }
+      if (keep) list[pos + __builtin_popcountll(mask & ((1ull << lane) - 1))] = (uint16_t)kb;
+      __syncthreads();
+    }
+  }
+  auto entry = [&](int i) { return SPARSE ? (int)__builtin_amdgcn_readfirstlane(list[i]) : i; };
+
+  DmaPlan<D, BLK> plan;
+  plan.init(__builtin_amdgcn_readfirstlane(wave), lane);
+  int kb = 0;
+  if (nu > 0) {
+    kb = entry(0);
+    issue_block<D, BLK>(plan, kh, lds_address(sk[0]), kb, n);
+    issue_block<D, BLK>(plan, vh, lds_address(sv[0]), kb, n);
+  }
+  WaveState<D, BLK> st;
+  {
+    const bf16x8* src = (const bf16x8*)(q + off + (size_t)min(row, n - 1) * D) + h;
+#pragma unroll
+    for (int cc = 0; cc < T::DC; cc++) st.q[cc] = src[2 * cc];
+#pragma unroll
+    for (int cc = 0; cc < T::DC; cc++)
+      st.q[cc] = __builtin_convertvector(__builtin_convertvector(st.q[cc], f32x8) * c, bf16x8);
+#pragma unroll
+    for (int cc = 0; cc < T::DC; cc++) asm volatile("" ::"v"(st.q[cc]));
+  }
+  st.m = -__builtin_inff();
+  st.l = 0.0f;
+  st.set_neg_max(0.0f);
+  int fresh = 1;
+#pragma unroll
+  for (int dt = 0; dt < T::DT; dt++) st.o[dt] = (f32x16){};
+
+  const int k0 = grp * HK;
+  const uint64_t* masks = (const uint64_t*)(ws + pv.masks);
+  for (int i = 0; i < nu; i++) {
+    uint64_t lo = ~0ull, hi = ~0ull;
+    bool tail;
+    if constexpr (PAD) {
+      lo = masks[2 * kb];
+      hi = masks[2 * kb + 1];
+      tail = (lo & hi) != ~0ull;
+    } else {
+      tail = (kb + 1) * BLK > n;
+    }
+    wait_dma<0>();                                        // block i, issued a block ago
+    __syncthreads();                                      // ... by every wave; block i-1 read
+    const int cur = kb;
+    const bool more = i + 1 < nu;
+    if (more) {
+      kb = entry(i + 1);
+      issue_block<D, BLK>(plan, kh, lds_address(sk[(i + 1) & 1]), kb, n);
+    }
+    f32x16 s[H::KT];
+    qk_half<D, BLK, HK>(st, s, sk[i & 1], k0, lane);
+    if (more) issue_block<D, BLK>(plan, vh, lds_address(sv[(i + 1) & 1]), kb, n);
+    softmax_pv_half<D, BLK, PAD, HK>(st, s, sv[i & 1], cur, k0, n, tail, lo, hi, lane, fresh);
+  }
+
+  // Merge: both groups scale their O to the common base; group g finishes columns 32 DH g .., adding
+  // what the other group holds of them.
+  const float mine = pair_sum(st.l);
+  if (h == 0) stat[wave][r32] = make_float2(st.m, mine);
+  __syncthreads();                                        // (also: the buffers are no longer read)
+  const float2 other = stat[(1 - grp) * T::kWaves + gw][r32];
+  const float top = fmaxf(st.m, other.x);
+  const float alpha = st.m == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(st.m - top);
+  const float beta = other.x == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(other.x - top);
+  const float lsum = mine * alpha + other.y * beta;
+  const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+  static_assert(W * DH * 4096 <= 4 * T::BYTES, "a wave's half of O fits its share of the buffers");
+  constexpr int kPer = T::BYTES / (DH * 4096);            // waves per buffer
+  auto slot = [&](int w) { return (f32x4*)((w / kPer < 2 ? sk[w / kPer] : sv[w / kPer - 2]) + (w % kPer) * DH * 4096) + lane; };
+  f32x4* out = slot(wave);
+#pragma unroll
+  for (int j = 0; j < DH; j++)
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      const f32x16& x = st.o[j], &y = st.o[DH + j];
+      const int e = 4 * a;
+      const f32x4 lower = {x[e], x[e + 1], x[e + 2], x[e + 3]}, upper = {y[e], y[e + 1], y[e + 2], y[e + 3]};
+      out[(j * 4 + a) * 64] = (grp == 0 ? upper : lower) * alpha;
+    }
+  __syncthreads();
+  const f32x4* in = slot((1 - grp) * T::kWaves + gw);
+  __bf16* dst = o + off + (size_t)row * D + 32 * DH * grp + 4 * h;
+#pragma unroll
+  for (int j = 0; j < DH; j++)
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      const f32x16& x = st.o[j], &y = st.o[DH + j];
+      const int e = 4 * a;
+      const f32x4 lower = {x[e], x[e + 1], x[e + 2], x[e + 3]}, upper = {y[e], y[e + 1], y[e + 2], y[e + 3]};
+      const f32x4 sum = ((grp == 0 ? lower : upper) * alpha + in[(j * 4 + a) * 64]) * inv;
+      if (row < n) *(bf16x4*)(dst + 32 * j + 8 * a) = __builtin_convertvector(sum, bf16x4);
+    }
+  if (lse && grp == 0 && h == 0 && row < n)
+    lse[(size_t)bh * n + row] = lsum > 0.0f ? (top + __builtin_log2f(lsum)) * 0.69314718055994530942f
+                                            : -__builtin_inff();
+}
+
 // Workgroups of a persistent grid over n_items work items: as many as fit the device at once (the
 // key list, 2 nb bytes of LDS, can allow fewer than the registers do), but no more than there are
 // items -- beyond one workgroup per CU the dispatcher stacks them, and of two stacked workgroups
@@ -2443,15 +2631,21 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
                                   void* workspace, const WorkspaceLayout& wl, int32_t cus,
                                   hipStream_t stream, bool rearm) {
   char* ws = (char*)workspace;
+  static_assert(sizeof(PlanHeader) <= 256, "the plan header is the workspace's first section");
+  const PlanView pv = {(uint32_t)wl.params, (uint32_t)wl.coords, (uint32_t)wl.order, (uint32_t)wl.queues,
+                       (uint32_t)(PAD ? wl.masks : 0), (uint32_t)wl.pairs, (uint32_t)wl.starts};
+  if (split_rows(expect.n_bh, expect.nb, BLK * SUB)) {
+    hipLaunchKernelGGL((psa_split_kernel<D, BLK * SUB, true, PAD>), dim3(expect.n_bh * expect.nb),
+                       dim3(4 * BLK * SUB), 0, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
+                       (__bf16*)o, lse, (const uint8_t*)ws, pv, expect, c);
+    return hipGetLastError();
+  }
   if (rearm) {
     hipLaunchKernelGGL(psa_rearm_kernel, dim3(1), dim3(64), 0, stream, (int32_t*)(ws + wl.queues),
                        (const PlanHeader*)(ws + wl.header), expect);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  static_assert(sizeof(PlanHeader) <= 256, "the plan header is the workspace's first section");
-  const PlanView pv = {(uint32_t)wl.params, (uint32_t)wl.coords, (uint32_t)wl.order, (uint32_t)wl.queues,
-                       (uint32_t)(PAD ? wl.masks : 0), (uint32_t)wl.pairs, (uint32_t)wl.starts};
   const int32_t list_bytes = D == 64 ? (2 * expect.nb + 15) & ~15 : 0;
   const int32_t grid = pair_grid<D, BLK>(cus, expect.n_bh * pairs_per_head(expect.nb) * SUB, list_bytes);
   hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, true, PAD>), dim3(grid), dim3(4 * BLK), list_bytes, stream,
@@ -2490,7 +2684,8 @@ hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, f
 // Dense attention.  With queues (a dense workspace) a one-thread-group kernel arms them and a
 // persistent grid takes the items; without, one workgroup per item.  The items are pairs of
 // 128-row blocks at either block size: every block is kept, so the block size changes neither the
-// keys of a row nor their order, and both give the same bits.
+// keys of a row nor their order, and both give the same bits.  (Few query blocks run on the split
+// engine, which reads no queues.)
 template <int D, int BLK, int SUB>
 static hipError_t launch_dense_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                  int32_t n_bh, int32_t n, float c, int32_t* queues, int32_t cus,
@@ -2516,9 +2711,25 @@ static hipError_t launch_dense_t(const void* q, const void* k, const void* v, vo
 }
 
 hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, float* lse,
-                        int32_t batch, int32_t n_heads, int32_t head_dim, int32_t n_tokens, float c,
-                        int32_t* queues, int32_t cus, hipStream_t stream) {
+                        int32_t batch, int32_t n_heads, int32_t head_dim, int32_t n_tokens,
+                        int32_t block, float c, int32_t* queues, int32_t cus, hipStream_t stream) {
   const int32_t n_bh = batch * n_heads;
+  const int32_t nb = (n_tokens + block - 1) / block;
+  if (split_rows(n_bh, nb, block)) {
+    PlanHeader e = {};
+    e.n_bh = n_bh;
+    e.n_heads = n_bh;
+    e.nb = nb;
+    e.n = n_tokens;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(n_bh * nb), dim3(4 * block), 0, stream, (const __bf16*)q, (const __bf16*)k,
+                         (const __bf16*)v, (__bf16*)o, lse, (const uint8_t*)nullptr, PlanView{}, e, c);
+      return hipGetLastError();
+    };
+    if (block == 128)
+      return head_dim == 128 ? go(psa_split_kernel<128, 128, false, false>) : go(psa_split_kernel<64, 128, false, false>);
+    return head_dim == 128 ? go(psa_split_kernel<128, 64, false, false>) : go(psa_split_kernel<64, 64, false, false>);
+  }
   if (head_dim == 128)
     return launch_dense_t<128, 128, 1>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
   if (head_dim == 64)

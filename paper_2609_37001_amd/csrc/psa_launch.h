@@ -133,7 +133,7 @@ hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, f
 // (one workgroup per work item).
 hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, float* lse,
                         int32_t batch, int32_t n_heads, int32_t head_dim, int32_t n_tokens,
-                        float scale_log2, int32_t* queues, int32_t cus, hipStream_t stream);
+                        int32_t block, float scale_log2, int32_t* queues, int32_t cus, hipStream_t stream);
 
 // Device address of the static scratch of psa_attention_fwd_noalloc on the current device
 // (PSA_NOALLOC_SCRATCH_BYTES, 256-byte aligned), looked up once per device.
