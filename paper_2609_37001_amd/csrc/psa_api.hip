@@ -207,6 +207,28 @@ psa_status_t check_plan_3d(int32_t batch, int32_t n_heads, psa_grid_t grid, psa_
   return check_work(batch, n_heads, workspace, workspace_bytes, g, wl);
 }
 
+// Whether an axis of `extent` positions keeps every distance: the residues of |delta - offset|, which
+// takes every value of [lo, hi], all lie below the width.
+bool axis_full(int32_t w, int32_t o, int32_t s, int32_t extent) {
+  if (w >= s) return true;
+  const int64_t a = o < 0 ? -(int64_t)o : o, lo = std::max<int64_t>(0, a - (extent - 1)), hi = a + extent - 1;
+  return lo % s + (hi - lo) < w;
+}
+
+// Whether every head keeps every key block.  Never for PSABlocks (their dense counterpart runs on
+// another sequence).  Where a block is longer than a frame not every frame starts one, so stripes
+// that miss only distances no two blocks have would pass for sparse: such grids count as full.
+bool plan_full(const psa::Geometry& g, const psa_stripe_t* params, int32_t n_heads) {
+  if (g.pbt > 0) return false;
+  if (g.block > g.hw) return true;
+  const int32_t slots = (g.hw - 1) / g.block + 1;
+  for (int32_t h = 0; h < n_heads; h++)
+    if (!axis_full(params[h].t_w, params[h].t_o, params[h].t_s, g.frames) ||
+        !axis_full(params[h].s_w, params[h].s_o, params[h].s_s, slots))
+      return false;
+  return true;
+}
+
 // The kernels of a plan over geometry g.
 psa_status_t enqueue_plan(int32_t batch, int32_t n_heads, const psa::Geometry& g,
                           const psa_stripe_t* params, void* workspace,
@@ -215,7 +237,8 @@ psa_status_t enqueue_plan(int32_t batch, int32_t n_heads, const psa::Geometry& g
   psa::ParamChunk chunks[(PSA_MAX_BATCH_HEADS + psa::kHeadsPerChunk - 1) / psa::kHeadsPerChunk];
   for (int32_t h0 = 0; h0 < n_heads; h0 += psa::kHeadsPerChunk)
     chunks[h0 / psa::kHeadsPerChunk] = chunk_of(params, h0, n_heads);
-  const hipError_t e = psa::launch_plan(chunks, g, batch, n_heads, workspace, wl, kept_per_row, stream);
+  const hipError_t e = psa::launch_plan(chunks, g, batch, n_heads, plan_full(g, params, n_heads), workspace, wl,
+                                         kept_per_row, stream);
   return e == hipSuccess ? PSA_OK : hip_fail(e, who);
 }
 
@@ -239,12 +262,11 @@ int32_t compute_units() {
   return cus;
 }
 
-// The run of a plan; `rearm` = false right after the plan's own kernels, which leave the queue
-// counters at zero.
+// The run of a plan; right after the plan's own kernels `params` are the plan's, else null.
 psa_status_t run_planned(const void* q, const void* k, const void* v, void* o, int32_t batch,
                          int32_t n_heads, int32_t head_dim, psa_grid_t grid, int32_t block,
                          float softmax_scale, void* workspace, size_t workspace_bytes, float* lse,
-                         hipStream_t stream, bool rearm) {
+                         hipStream_t stream, const psa_stripe_t* params) {
   psa_status_t s = check_tensors(q, k, v, o, lse);
   if (s != PSA_OK) return s;
   s = check_attention_shape(batch, n_heads, head_dim, block);
@@ -255,7 +277,8 @@ psa_status_t run_planned(const void* q, const void* k, const void* v, void* o, i
   if (s != PSA_OK) return s;
   const float c = softmax_scale * 1.4426950408889634f;
   hipError_t e = psa::launch_sparse(q, k, v, o, lse, batch, n_heads, head_dim, g, c, workspace, wl,
-                                    compute_units(), stream, rearm);
+                                    compute_units(), stream,
+                                    params ? (int32_t)plan_full(g, params, n_heads) : -1);
   if (e != hipSuccess) return hip_fail(e, "psa_attention_run kernel launch");
   return PSA_OK;
 }
@@ -366,7 +389,7 @@ psa_status_t psa_attention_run_3d(const void* q, const void* k, const void* v, v
   if (s != PSA_OK) return s;
   const float c = softmax_scale * 1.4426950408889634f;
   hipError_t e = psa::launch_sparse(q, k, v, o, lse, batch, n_heads, head_dim, g, c, workspace, wl,
-                                    compute_units(), stream);
+                                    compute_units(), stream, -1);
   if (e != hipSuccess) return hip_fail(e, "psa_attention_run_3d kernel launch");
   return PSA_OK;
 }
@@ -413,7 +436,7 @@ psa_status_t psa_attention_run(const void* q, const void* k, const void* v, void
                                int32_t block, float softmax_scale, void* workspace,
                                size_t workspace_bytes, float* lse, hipStream_t stream) {
   return run_planned(q, k, v, o, batch, n_heads, head_dim, grid, block, softmax_scale, workspace,
-                     workspace_bytes, lse, stream, true);
+                     workspace_bytes, lse, stream, nullptr);
 }
 
 psa_status_t psa_attention_fwd(const void* q, const void* k, const void* v, void* o,
@@ -429,7 +452,7 @@ psa_status_t psa_attention_fwd(const void* q, const void* k, const void* v, void
                          kept_per_row, stream);
   if (s != PSA_OK) return s;
   return run_planned(q, k, v, o, batch, n_heads, head_dim, grid, block, softmax_scale, workspace,
-                     workspace_bytes, lse, stream, false);
+                     workspace_bytes, lse, stream, params);
 }
 
 psa_status_t psa_attention_fwd_noalloc(const void* q, const void* k, const void* v, void* o,

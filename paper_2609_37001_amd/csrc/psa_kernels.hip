@@ -1534,14 +1534,24 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   h.pbt = g.pbt;
   h.pbh = g.pbh;
   h.pbw = g.pbw;
+  h.full = -1;
   return h;
 }
 
-// Whether this many query blocks run on the split engine: at most one workgroup per CU at block
-// 128 and two of the half as large ones at block 64, on the 256 CUs of an MI355X (a fixed number:
-// the plan and every later run have to agree, and the sparse and the dense path round alike).
-static bool split_rows(int32_t n_bh, int32_t nb, int32_t block) {
-  return (int64_t)n_bh * nb <= 256 * (128 / block);
+// Which problems run on the split engine, by their query blocks; the lines are for the 256 CUs of an
+// MI355X (fixed numbers: a plan and its runs have to agree).
+//  * Up to one workgroup per CU (at block 64, two of the half as large ones): always.
+//  * Up to two: unless every head keeps every key block.  Rows of unequal length gain 1.0 to 1.75
+//    times over pairs (28 drawn calls: 1.08 in the mean), because the longest pair sets the time;
+//    rows of equal length lose up to 13 %, two rounds of half the work and more for one.  The dense
+//    path therefore stays on pairs, and so does the sparse path at full density, where it returns
+//    the dense path's bits.
+//    Beyond two the longest-first list of pairs is 2 % faster in the mean (24 drawn calls).
+static bool split_any(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 256 * (128 / block); }
+static bool split_sparse(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 512 * (128 / block); }
+// Whether no run of this plan needs pairs.
+static bool split_plan(int32_t n_bh, int32_t nb, int32_t block, bool full) {
+  return split_any(n_bh, nb, block) || (!full && split_sparse(n_bh, nb, block));
 }
 
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
@@ -1558,7 +1568,7 @@ static bool ranked(const Geometry& g, int32_t n_items) { return n_items <= (g.bl
 static bool head_planned(const Geometry& g) { return g.nb <= kHeadPlanRows; }
 
 hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batch, int32_t n_heads,
-                       void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
+                       bool full, void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
                        hipStream_t stream) {
   char* ws = (char*)workspace;
   PlanHeader* header = (PlanHeader*)(ws + wl.header);
@@ -1569,8 +1579,9 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const int32_t per_head = pairs_per_head(g.nb), n_items = batch * n_heads * per_head;
   const int32_t n_chunks = (n_heads + kHeadsPerChunk - 1) / kHeadsPerChunk;
   const bool blocks3d = g.pbt > 0, fused = head_planned(g) && ranked(g, n_items);
-  const bool split = split_rows(batch * n_heads, g.nb, g.block);
-  const PlanHeader done = plan_header(g, batch, n_heads);
+  const bool split = split_plan(batch * n_heads, g.nb, g.block, full);
+  PlanHeader done = plan_header(g, batch, n_heads);
+  done.full = full;
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -1974,12 +1985,13 @@ __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
   __builtin_amdgcn_s_setprio(0);
 }
 
-// Whether a workspace holds a finished plan for exactly the sizes of this launch.
+// Whether a workspace holds a finished plan for exactly the sizes of this launch (and, unless
+// e.full < 0, of that density).
 __device__ __forceinline__ bool plan_matches(const PlanHeader& h, const PlanHeader& e) {
   return h.magic == kPlanMagic && h.n_bh == e.n_bh && h.n_heads == e.n_heads && h.nb == e.nb &&
          h.block == e.block && h.n == e.n && h.frames == e.frames && h.height == e.height &&
          h.width == e.width && h.n_text == e.n_text && h.pbt == e.pbt && h.pbh == e.pbh &&
-         h.pbw == e.pbw;
+         h.pbw == e.pbw && (e.full < 0 || h.full == e.full);
 }
 
 // Pops the next work item of the persistent schedule (one lane): from queue `queue` first, then
@@ -2463,8 +2475,8 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
 // 24 drawn calls of this size.
 // ---------------------------------------------------------------------------------------------
 
-// Key blocks of the longest sequence the split engine takes.
-constexpr int kSplitBlocks = 512;
+// Key blocks of the longest sequence the split engine takes (split_sparse: one head of 1024 blocks at block 64).
+constexpr int kSplitBlocks = 1024;
 
 template <int D, int BLK, bool SPARSE, bool PAD>
 __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2))) void psa_split_kernel(
@@ -2481,8 +2493,16 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
   __shared__ float2 stat[W][32];              // (m, l) of every wave's rows
 
   if constexpr (SPARSE) {
-    // A workspace without a finished plan for exactly these sizes is left alone.
-    if (!plan_matches(*(const PlanHeader*)ws, expect)) return;
+    // A workspace without a finished plan for exactly these sizes is left alone.  If only the density
+    // differs, the pair engine is launched next: its queue counters are set here.
+    if (!plan_matches(*(const PlanHeader*)ws, expect)) {
+      PlanHeader dense = expect;
+      dense.full = 1;
+      if (expect.full == 0 && blockIdx.x == 0 && threadIdx.x < kNumQueues &&
+          plan_matches(*(const PlanHeader*)ws, dense))
+        ((int32_t*)(ws + pv.queues))[kQueueCounters + threadIdx.x * kCounterStride] = 0;
+      return;
+    }
   }
   const int32_t n_heads = expect.n_heads, n = expect.n, nb = expect.nb;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, gw = wave & (T::kWaves - 1);
@@ -2627,18 +2647,29 @@ static int32_t pair_grid(int32_t cus, int32_t n_items, int32_t list_bytes) {
 
 template <int D, int BLK, int SUB, bool PAD>
 static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, void* o,
-                                  float* lse, const PlanHeader& expect, float c,
+                                  float* lse, const PlanHeader& sizes, float c,
                                   void* workspace, const WorkspaceLayout& wl, int32_t cus,
-                                  hipStream_t stream, bool rearm) {
+                                  hipStream_t stream, int32_t full) {
   char* ws = (char*)workspace;
   static_assert(sizeof(PlanHeader) <= 256, "the plan header is the workspace's first section");
   const PlanView pv = {(uint32_t)wl.params, (uint32_t)wl.coords, (uint32_t)wl.order, (uint32_t)wl.queues,
                        (uint32_t)(PAD ? wl.masks : 0), (uint32_t)wl.pairs, (uint32_t)wl.starts};
-  if (split_rows(expect.n_bh, expect.nb, BLK * SUB)) {
+  PlanHeader expect = sizes;
+  bool rearm = full < 0;
+  const bool any = split_any(expect.n_bh, expect.nb, BLK * SUB);
+  if (any || (full != 1 && split_sparse(expect.n_bh, expect.nb, BLK * SUB))) {
+    // Of a run, whose plan's density only the device knows, both engines are launched beyond the
+    // sizes that are split at any density, and the one that does not fit the plan returns at once
+    // (PSABlock plans are never full).
+    const bool both = !PAD && !any && full < 0;
+    if (both) expect.full = 0;
     hipLaunchKernelGGL((psa_split_kernel<D, BLK * SUB, true, PAD>), dim3(expect.n_bh * expect.nb),
                        dim3(4 * BLK * SUB), 0, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                        (__bf16*)o, lse, (const uint8_t*)ws, pv, expect, c);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !both) return e;
+    expect.full = 1;
+    rearm = false;
   }
   if (rearm) {
     hipLaunchKernelGGL(psa_rearm_kernel, dim3(1), dim3(64), 0, stream, (int32_t*)(ws + wl.queues),
@@ -2657,27 +2688,27 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
                          int32_t batch, int32_t n_heads, int32_t head_dim, const Geometry& g,
                          float c, void* workspace, const WorkspaceLayout& wl, int32_t cus,
-                         hipStream_t stream, bool rearm) {
+                         hipStream_t stream, int32_t full) {
   const PlanHeader e = plan_header(g, batch, n_heads);
   if (g.pbt > 0) {
     if (head_dim == 128 && g.block == 128)
-      return launch_sparse_t<128, 128, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+      return launch_sparse_t<128, 128, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
     if (head_dim == 64 && g.block == 64)
-      return launch_sparse_t<64, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+      return launch_sparse_t<64, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
     if (head_dim == 128 && g.block == 64)
-      return launch_sparse_t<128, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+      return launch_sparse_t<128, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
     if (head_dim == 64 && g.block == 128)
-      return launch_sparse_t<64, 64, 2, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+      return launch_sparse_t<64, 64, 2, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
     return hipErrorInvalidValue;
   }
   if (head_dim == 128 && g.block == 128)
-    return launch_sparse_t<128, 128, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+    return launch_sparse_t<128, 128, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
   if (head_dim == 64 && g.block == 64)
-    return launch_sparse_t<64, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+    return launch_sparse_t<64, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
   if (head_dim == 128 && g.block == 64)
-    return launch_sparse_t<128, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+    return launch_sparse_t<128, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
   if (head_dim == 64 && g.block == 128)
-    return launch_sparse_t<64, 64, 2, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, rearm);
+    return launch_sparse_t<64, 64, 2, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
   return hipErrorInvalidValue;
 }
 
@@ -2715,7 +2746,7 @@ hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, fl
                         int32_t block, float c, int32_t* queues, int32_t cus, hipStream_t stream) {
   const int32_t n_bh = batch * n_heads;
   const int32_t nb = (n_tokens + block - 1) / block;
-  if (split_rows(n_bh, nb, block)) {
+  if (split_any(n_bh, nb, block)) {
     PlanHeader e = {};
     e.n_bh = n_bh;
     e.n_heads = n_bh;

@@ -54,6 +54,7 @@ struct PlanHeader {
   int32_t n;
   int32_t frames, height, width, n_text;
   int32_t pbt, pbh, pbw;
+  int32_t full;     // every head keeps every key block (or may, see plan_full)
 };
 
 // Layout of the queue area (int32 words): kNumQueues + 1 boundaries in the first 128-byte line,
@@ -121,13 +122,15 @@ hipError_t launch_layout(const void* src, void* dst, int32_t n_bh, int32_t head_
 // The plan: stripe parameters (chunks of kHeadsPerChunk heads) and block coordinates, the pairs of
 // query blocks, their work and their order; the header last.
 hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batch, int32_t n_heads,
-                       void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
+                       bool full, void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
                        hipStream_t stream);
 
+// full: right after the plan's own kernels its PlanHeader::full (they leave the queue counters at zero);
+// -1 for a run of an earlier plan, whose counters are set first.
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
                          int32_t batch, int32_t n_heads, int32_t head_dim, const Geometry& g,
                          float scale_log2, void* workspace, const WorkspaceLayout& wl,
-                         int32_t cus, hipStream_t stream, bool rearm = true);
+                         int32_t cus, hipStream_t stream, int32_t full);
 
 // queues: the int32 [kQueueWords] queue area of a dense workspace (persistent grid), or nullptr
 // (one workgroup per work item).

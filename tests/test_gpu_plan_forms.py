@@ -26,8 +26,14 @@ def stripes(heads, f, sp, seed):
     return out[:heads]
 
 
-# batch, heads, (F, H, W, text), block, head_dim
-CASES = [(1, 1, (1, 1, 7, 0), 64, 64), (2, 3, (1, 8, 16, 0), 128, 128), (1, 3, (2, 8, 16, 5), 128, 64),
+# batch, heads, (F, H, W, text), block, head_dim.  The first lines are the sizes at which a call changes
+# between the split engine (up to 256 query blocks, 512 unless every head keeps every block; twice as
+# many at block 64) and the pair engine.
+CASES = [(1, 4, (4, 8, 256, 0), 128, 128), (1, 4, (4, 8, 256, 1), 128, 128), (1, 4, (8, 8, 256, 0), 128, 64),
+         (1, 4, (8, 8, 256, 1), 128, 64), (2, 4, (4, 8, 128, 0), 64, 64), (2, 4, (4, 8, 128, 2), 64, 128),
+         (2, 4, (8, 8, 128, 0), 64, 128), (2, 4, (8, 8, 128, 3), 64, 64), (1, 1, (64, 8, 128, 0), 64, 64),
+         (1, 1, (64, 8, 128, 0), 128, 128),
+         (1, 1, (1, 1, 7, 0), 64, 64), (2, 3, (1, 8, 16, 0), 128, 128), (1, 3, (2, 8, 16, 5), 128, 64),
          (1, 4, (16, 8, 128, 0), 128, 128), (1, 4, (16, 8, 128, 1), 128, 128), (2, 4, (16, 8, 64, 0), 64, 128),
          (1, 64, (3, 8, 24, 3), 64, 64), (2, 65, (3, 8, 24, 3), 64, 64), (1, 65, (3, 4, 11, 0), 128, 128),
          (1, 64, (64, 8, 64, 0), 64, 64), (1, 65, (64, 8, 64, 0), 64, 64),
@@ -60,3 +66,26 @@ def test_every_row_once(case):
     fin = np.broadcast_to(keys > 0, got.shape)
     assert np.abs(got[fin] - np.broadcast_to(want, got.shape)[fin]).max() <= 2e-5
     assert t.equal(o, t.from_numpy(np.where(keys > 0, 0.5, 0.0)).to(o)[None, :, :, None].expand_as(o))
+
+
+@pytest.mark.parametrize("grid,heads", [((4, 8, 256, 0), 4), ((4, 8, 256, 0), 6), ((4, 8, 256, 9), 8), ((2, 3, 5, 2), 300)])
+@pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_full_density_same_bits_as_dense(d, block, grid, heads):
+    """At full density the sparse path (both calls of it, and a run whose density only the device knows)
+    returns the dense path's bits, on either engine; with one head thinned it does not depend on the
+    call either."""
+    t = gu.torch()
+    f, h, w, nt = grid
+    n = f * h * w + nt
+    gen = t.Generator(device="cuda").manual_seed(9)
+    q, k, v = (t.randn((1, heads, n, d), generator=gen, device="cuda", dtype=t.bfloat16) for _ in range(3))
+    full = [(f, 0, INF, -(-(h * w) // block), 0, INF) if i % 2 else (1, 3, 1, 2, -1, 2) for i in range(heads)]
+    dense, dense_lse = psa.dense_fwd(q, k, v, block, return_lse=True)
+    for params in (full, full[:-1] + [(1, 0, INF, 1, 0, INF)]):
+        o, lse = psa.attention_fwd(q, k, v, grid, block, params, return_lse=True)
+        ws = psa.plan(params, grid, block)
+        for _ in range(2):
+            o2, lse2 = psa.run(q, k, v, grid, block, ws, return_lse=True, out=t.full_like(q, float("nan")))
+            assert t.equal(o, o2) and t.equal(lse, lse2)
+        if params is full:
+            assert t.equal(o, dense) and t.equal(lse, dense_lse)
