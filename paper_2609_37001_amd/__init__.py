@@ -73,12 +73,12 @@ def _on(stream):
 
 
 def ctypes_void(x):
-    import ctypes
-    return ctypes.c_void_p(int(x)) if x else None
+    """A pointer argument (the library's argument types take plain integers; 0 is NULL)."""
+    return int(x) if x else None
 
 
 def _ptr(t):
-    return ctypes_void(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _check_qkv(*ts):
@@ -157,19 +157,20 @@ def attention_fwd(q, k, v, grid, block, params, scale=None, out=None, return_lse
         raise ValueError("one stripe tuple per head is required")
     _check_tokens(n, grid)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
-    nb = num_blocks(grid, block)
     with torch.cuda.device(q.device), _on(stream):
         o = torch.empty_like(q) if out is None else out
         _check_qkv(q, o)
         lse = torch.empty((b, h, n), dtype=torch.float32, device=q.device) if return_lse else None
-        kept = torch.empty((h, max(nb, 1)), dtype=torch.int32, device=q.device) if return_kept_per_row else None
+        kept = None
+        if return_kept_per_row:
+            kept = torch.empty((h, max(num_blocks(grid, block), 1)), dtype=torch.int32, device=q.device)
         ws = workspace if workspace is not None else Workspace(b, h, grid, block, q.device)
         _lib.check(_lib.lib().psa_attention_fwd(
             _ptr(q), _ptr(k), _ptr(v), _ptr(o), b, h, d, _grid(grid), int(block),
             _lib.stripes(params), scale, _ptr(ws.tensor), ws.nbytes, _ptr(lse), _ptr(kept),
             _stream(None, q.device)))
     ws.sizes = (b, h, _grid_tuple(grid), int(block))
-    ws.params = [tuple(int(x) for x in m) for m in params]
+    ws.params = [tuple(map(int, m)) for m in params]
     res = (o,)
     if return_lse:
         res += (lse,)
@@ -221,7 +222,7 @@ def plan(params, grid, block, batch=1, device=None, workspace=None, return_kept_
                                                  _lib.stripes(params), _ptr(ws.tensor), ws.nbytes,
                                                  _ptr(kept), _stream(None, device)))
     ws.sizes = (int(batch), h, _grid_tuple(grid), int(block))
-    ws.params = [tuple(int(x) for x in m) for m in params]
+    ws.params = [tuple(map(int, m)) for m in params]
     return (ws, kept) if return_kept_per_row else ws
 
 
@@ -370,7 +371,7 @@ def plan_3d(params, grid, pb, tile=128, batch=1, device=None, workspace=None,
                                                     int(tile), _lib.stripes(params), _ptr(ws.tensor),
                                                     ws.nbytes, _ptr(kept), _stream(None, device)))
     ws.sizes = (int(batch), h, _grid_tuple(grid), tuple(int(x) for x in pb), int(tile))
-    ws.params = [tuple(int(x) for x in m) for m in params]
+    ws.params = [tuple(map(int, m)) for m in params]
     return (ws, kept) if return_kept_per_tile else ws
 
 

@@ -4,7 +4,9 @@ attention path runs in the HIP kernels of the library; torch supplies device mem
 The library is loaded from this package directory; if it is missing the import of the binding
 functions raises, there is no fallback.
 """
+import array
 import ctypes
+import itertools
 import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -131,6 +133,13 @@ def check(status):
 
 def stripes(params):
     """Host array of psa_stripe_t from a sequence of 6-tuples."""
+    try:
+        # The usual form, packed at once (a third of the time); anything else goes element by element.
+        if set(map(len, params)) == {6}:
+            flat = array.array("i", list(map(int, itertools.chain.from_iterable(params))))
+            return (Stripe * len(params)).from_buffer(flat)
+    except (TypeError, OverflowError):
+        pass
     arr = (Stripe * max(1, len(params)))()
     for i, m in enumerate(params):
         arr[i] = Stripe(*[int(x) for x in m])
