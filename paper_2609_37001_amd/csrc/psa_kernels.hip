@@ -1534,7 +1534,6 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   h.pbt = g.pbt;
   h.pbh = g.pbh;
   h.pbw = g.pbw;
-  h.full = -1;
   return h;
 }
 
@@ -1549,6 +1548,10 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
 //    Beyond two the longest-first list of pairs is 2 % faster in the mean (24 drawn calls).
 static bool split_any(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 256 * (128 / block); }
 static bool split_sparse(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 512 * (128 / block); }
+// Whether the density decides; such a plan's header says which it is (kPlanMagicFull).
+static bool split_by_density(int32_t n_bh, int32_t nb, int32_t block) {
+  return split_sparse(n_bh, nb, block) && !split_any(n_bh, nb, block);
+}
 // Whether no run of this plan needs pairs.
 static bool split_plan(int32_t n_bh, int32_t nb, int32_t block, bool full) {
   return split_any(n_bh, nb, block) || (!full && split_sparse(n_bh, nb, block));
@@ -1581,7 +1584,7 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const bool blocks3d = g.pbt > 0, fused = head_planned(g) && ranked(g, n_items);
   const bool split = split_plan(batch * n_heads, g.nb, g.block, full);
   PlanHeader done = plan_header(g, batch, n_heads);
-  done.full = full;
+  if (split_by_density(batch * n_heads, g.nb, g.block) && full) done.magic = kPlanMagicFull;
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -1985,13 +1988,12 @@ __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
   __builtin_amdgcn_s_setprio(0);
 }
 
-// Whether a workspace holds a finished plan for exactly the sizes of this launch (and, unless
-// e.full < 0, of that density).
+// Whether a workspace holds a finished plan for exactly the sizes of this launch.
 __device__ __forceinline__ bool plan_matches(const PlanHeader& h, const PlanHeader& e) {
-  return h.magic == kPlanMagic && h.n_bh == e.n_bh && h.n_heads == e.n_heads && h.nb == e.nb &&
+  return h.magic == e.magic && h.n_bh == e.n_bh && h.n_heads == e.n_heads && h.nb == e.nb &&
          h.block == e.block && h.n == e.n && h.frames == e.frames && h.height == e.height &&
          h.width == e.width && h.n_text == e.n_text && h.pbt == e.pbt && h.pbh == e.pbh &&
-         h.pbw == e.pbw && (e.full < 0 || h.full == e.full);
+         h.pbw == e.pbw;
 }
 
 // Pops the next work item of the persistent schedule (one lane): from queue `queue` first, then
@@ -2497,8 +2499,8 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // differs, the pair engine is launched next: its queue counters are set here.
     if (!plan_matches(*(const PlanHeader*)ws, expect)) {
       PlanHeader dense = expect;
-      dense.full = 1;
-      if (expect.full == 0 && blockIdx.x == 0 && threadIdx.x < kNumQueues &&
+      dense.magic = kPlanMagicFull;
+      if (blockIdx.x == 0 && threadIdx.x < kNumQueues &&
           plan_matches(*(const PlanHeader*)ws, dense))
         ((int32_t*)(ws + pv.queues))[kQueueCounters + threadIdx.x * kCounterStride] = 0;
       return;
@@ -2656,21 +2658,18 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
                        (uint32_t)(PAD ? wl.masks : 0), (uint32_t)wl.pairs, (uint32_t)wl.starts};
   PlanHeader expect = sizes;
   bool rearm = full < 0;
-  const bool any = split_any(expect.n_bh, expect.nb, BLK * SUB);
-  if (any || (full != 1 && split_sparse(expect.n_bh, expect.nb, BLK * SUB))) {
-    // Of a run, whose plan's density only the device knows, both engines are launched beyond the
-    // sizes that are split at any density, and the one that does not fit the plan returns at once
-    // (PSABlock plans are never full).
-    const bool both = !PAD && !any && full < 0;
-    if (both) expect.full = 0;
+  const bool by_density = split_by_density(expect.n_bh, expect.nb, BLK * SUB);
+  if (split_any(expect.n_bh, expect.nb, BLK * SUB) || (by_density && full != 1)) {
     hipLaunchKernelGGL((psa_split_kernel<D, BLK * SUB, true, PAD>), dim3(expect.n_bh * expect.nb),
                        dim3(4 * BLK * SUB), 0, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
                        (__bf16*)o, lse, (const uint8_t*)ws, pv, expect, c);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !both) return e;
-    expect.full = 1;
+    // Of a run, whose plan's density only the device knows, both engines are launched where it
+    // decides, and the one that does not fit the plan returns at once (PSABlock plans are never full).
+    if (e != hipSuccess || !by_density || full == 0 || PAD) return e;
     rearm = false;
   }
+  if (by_density) expect.magic = kPlanMagicFull;
   if (rearm) {
     hipLaunchKernelGGL(psa_rearm_kernel, dim3(1), dim3(64), 0, stream, (int32_t*)(ws + wl.queues),
                        (const PlanHeader*)(ws + wl.header), expect);

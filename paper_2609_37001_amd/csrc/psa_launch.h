@@ -44,9 +44,12 @@ constexpr int32_t kDeadTile = -2;
 
 // Identifies a finished plan in the workspace header; the sizes it was made for follow it.
 constexpr uint32_t kPlanMagic = 0x50534131u;  // "PSA1"
+// The same for a plan in which every head keeps every key block (or may, see plan_full), where the
+// engine of a run depends on that.
+constexpr uint32_t kPlanMagicFull = 0x50534132u;
 
 struct PlanHeader {
-  uint32_t magic;   // kPlanMagic once the plan's kernels have run, 0 while they run
+  uint32_t magic;   // kPlanMagic or kPlanMagicFull once the plan's kernels have run, 0 while they run
   int32_t n_bh;     // batch * n_heads
   int32_t n_heads;
   int32_t nb;
@@ -54,7 +57,6 @@ struct PlanHeader {
   int32_t n;
   int32_t frames, height, width, n_text;
   int32_t pbt, pbh, pbw;
-  int32_t full;     // every head keeps every key block (or may, see plan_full)
 };
 
 // Layout of the queue area (int32 words): kNumQueues + 1 boundaries in the first 128-byte line,
@@ -125,7 +127,7 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
                        bool full, void* workspace, const WorkspaceLayout& wl, int32_t* kept_per_row,
                        hipStream_t stream);
 
-// full: right after the plan's own kernels its PlanHeader::full (they leave the queue counters at zero);
+// full: right after the plan's own kernels whether it is full (they leave the queue counters at zero);
 // -1 for a run of an earlier plan, whose counters are set first.
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
                          int32_t batch, int32_t n_heads, int32_t head_dim, const Geometry& g,
