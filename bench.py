@@ -35,9 +35,9 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA peak (published)
 HBM_PEAK = 8.0e12             # MI355X HBM3E bandwidth, bytes/s (published)
-KERNEL = "psa_pair_kernel<128, 128, true, false>"       # the sparse attention at block 128
-KERNEL_3D = "psa_pair_kernel<128, 128, true, true>"     # ... with the 3D-padding masks
-ATTN_PREFIXES = ("psa_sparse_kernel", "psa_dense_kernel", "psa_pair_kernel")  # attention kernels
+KERNEL = "psa_pair_kernel<128, 128, 1, true, false>"    # the sparse attention at block 128
+KERNEL_3D = "psa_pair_kernel<128, 128, 1, true, true>"  # ... with the 3D-padding masks
+ATTN_PREFIXES = ("psa_pair_kernel<", "psa_split_kernel<")  # attention kernels
 COUNTERS_MD = os.path.join(ROOT, "profiles", "psa_pair_kernel_wan14b_counters.md")
 SOURCES = ("paper_2609_37001_amd/csrc/psa_kernels.hip", "paper_2609_37001_amd/csrc/psa_launch.h",
            "paper_2609_37001_amd/csrc/psa_api.hip", "paper_2609_37001_amd/build.py", "include/psa.h")
@@ -139,6 +139,13 @@ def time_calls(fn, steps, warmup, torch):
             "min": float(min(per))}
 
 
+def short_name(name):
+    """Kernel name without arguments and namespace; the parts per item of the pair kernel (its third
+    template argument) are left out where they are 1."""
+    name = name.split("(")[0].replace("void ", "").replace("psa::", "")
+    return re.sub(r"(psa_pair_kernel<\d+, \d+), 1, ", r"\1, ", name)
+
+
 def counter_rows(run_dir, counter):
     """{kernel name: [per-dispatch values]} of one counter in a rocprofv3 csv run directory."""
     out = {}
@@ -156,7 +163,7 @@ def summarise_counters(fetch_dir, write_dir, copy_mb):
     fetch, write = counter_rows(fetch_dir, "FETCH_SIZE"), counter_rows(write_dir, "WRITE_SIZE")
 
     def pick(rows, key):
-        hits = [v for k, v in rows.items() if key in k]
+        hits = [v for k, v in rows.items() if short_name(key) in short_name(k)]
         if not hits:
             raise SystemExit("no dispatch of %s in the counter runs" % key)
         return hits[0]
@@ -225,7 +232,7 @@ def trace_dispatches(trace_dir):
     rows = []
     with open(paths[0]) as f:
         for r in csv.DictReader(f):
-            name = r["Kernel_Name"].split("(")[0].replace("void ", "").replace("psa::", "")
+            name = short_name(r["Kernel_Name"])
             rows.append((int(r["Dispatch_Id"]), name, int(r["End_Timestamp"]) - int(r["Start_Timestamp"])))
     out = {}
     for _, name, ns in sorted(rows):
@@ -240,8 +247,8 @@ def trace_summary(trace_dir, bench_out, steps, warmup, dense_steps):
     trace's mean of the timed run-alone launches is set beside the one the run's JSON line
     reports (HIP events around the same launches)."""
     disp = trace_dispatches(trace_dir)
-    sparse = disp.get(KERNEL.replace("psa::", ""), [])
-    dense = disp.get(KERNEL.replace("true, false", "false, false"), [])
+    sparse = disp.get(short_name(KERNEL), [])
+    dense = disp.get(short_name(KERNEL.replace("true, false", "false, false")), [])
     expect = warmup + steps + 1 + steps
     if len(sparse) != expect:
         raise SystemExit("%d sparse launches in the trace, %d expected from --steps %d --warmup %d"
@@ -289,7 +296,7 @@ def utilisation_rows(sq_dir, tcc_dir, trace_dir, label):
         for path in glob.glob(os.path.join(run_dir, "**", "*counter_collection.csv"), recursive=True):
             with open(path) as f:
                 for r in csv.DictReader(f):
-                    name = r["Kernel_Name"].split("(")[0].replace("void ", "").replace("psa::", "")
+                    name = short_name(r["Kernel_Name"])
                     if name.startswith(ATTN_PREFIXES):
                         out.setdefault(name, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
         return {k: {c: sum(v) / len(v) for c, v in d.items()} for k, d in out.items()}
@@ -298,7 +305,7 @@ def utilisation_rows(sq_dir, tcc_dir, trace_dir, label):
     for path in glob.glob(os.path.join(trace_dir, "**", "*kernel_stats.csv"), recursive=True):
         with open(path) as f:
             for r in csv.DictReader(f):
-                dur[r["Name"].split("(")[0].replace("void ", "").replace("psa::", "")] = float(r["AverageNs"]) * 1e-9
+                dur[short_name(r["Name"])] = float(r["AverageNs"]) * 1e-9
     rows = []
     for k in sorted(sq):
         a, b, t = sq[k], tcc[k], dur[k]
@@ -330,14 +337,14 @@ def hbm_rows(fetch_dir, write_dir, trace_dir, cfg, copy_mb):
     for path in glob.glob(os.path.join(trace_dir, "**", "*kernel_stats.csv"), recursive=True):
         with open(path) as f:
             for r in csv.DictReader(f):
-                dur[r["Name"].split("(")[0].replace("void ", "").replace("psa::", "")] = float(r["AverageNs"]) * 1e-9
+                dur[short_name(r["Name"])] = float(r["AverageNs"]) * 1e-9
     algo = 8.0 * cfg.batch * cfg.heads * cfg.n_tokens * cfg.head_dim
     rows = []
     for full, vals in sorted(fetch.items()):
-        k = full.split("(")[0].replace("void ", "").replace("psa::", "")
+        k = short_name(full)
         if not k.startswith(ATTN_PREFIXES):
             continue
-        wv = [v for kk, v in write.items() if kk.split("(")[0].replace("void ", "").replace("psa::", "") == k][0]
+        wv = [v for kk, v in write.items() if short_name(kk) == k][0]
         rd = sum(vals) / len(vals) * 1024.0 * f_scale
         wr = sum(wv) / len(wv) * 1024.0 * w_scale
         t = dur[k]
@@ -358,7 +365,7 @@ def wait_rows(run_dir, label):
     for path in glob.glob(os.path.join(run_dir, "**", "*counter_collection.csv"), recursive=True):
         with open(path) as f:
             for r in csv.DictReader(f):
-                name = r["Kernel_Name"].split("(")[0].replace("void ", "").replace("psa::", "")
+                name = short_name(r["Kernel_Name"])
                 if name.startswith(ATTN_PREFIXES):
                     out.setdefault(name, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
     rows = []
