@@ -1521,7 +1521,7 @@ __global__ __launch_bounds__(1024) void psa_starts_kernel(
 
 static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads) {
   PlanHeader h;
-  h.magic = kPlanMagic;
+  h.magic = g.block == 64 ? kPlanMagic64 : kPlanMagic;
   h.n_bh = batch * n_heads;
   h.n_heads = n_heads;
   h.nb = g.nb;
@@ -1548,7 +1548,7 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
 //    Beyond two the longest-first list of pairs is 2 % faster in the mean (24 drawn calls).
 static bool split_any(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 256 * (128 / block); }
 static bool split_sparse(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 512 * (128 / block); }
-// Whether the density decides; such a plan's header says which it is (kPlanMagicFull).
+// Whether the density decides; such a plan's header says which it is (kPlanFull).
 static bool split_by_density(int32_t n_bh, int32_t nb, int32_t block) {
   return split_sparse(n_bh, nb, block) && !split_any(n_bh, nb, block);
 }
@@ -1584,7 +1584,7 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const bool blocks3d = g.pbt > 0, fused = head_planned(g) && ranked(g, n_items);
   const bool split = split_plan(batch * n_heads, g.nb, g.block, full);
   PlanHeader done = plan_header(g, batch, n_heads);
-  if (split_by_density(batch * n_heads, g.nb, g.block) && full) done.magic = kPlanMagicFull;
+  if (split_by_density(batch * n_heads, g.nb, g.block) && full) done.magic |= kPlanFull;
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -2499,7 +2499,7 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // differs, the pair engine is launched next: its queue counters are set here.
     if (!plan_matches(*(const PlanHeader*)ws, expect)) {
       PlanHeader dense = expect;
-      dense.magic = kPlanMagicFull;
+      dense.magic |= kPlanFull;
       if (blockIdx.x == 0 && threadIdx.x < kNumQueues &&
           plan_matches(*(const PlanHeader*)ws, dense))
         ((int32_t*)(ws + pv.queues))[kQueueCounters + threadIdx.x * kCounterStride] = 0;
@@ -2669,7 +2669,7 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
     if (e != hipSuccess || !by_density || full == 0 || PAD) return e;
     rearm = false;
   }
-  if (by_density) expect.magic = kPlanMagicFull;
+  if (by_density) expect.magic |= kPlanFull;
   if (rearm) {
     hipLaunchKernelGGL(psa_rearm_kernel, dim3(1), dim3(64), 0, stream, (int32_t*)(ws + wl.queues),
                        (const PlanHeader*)(ws + wl.header), expect);

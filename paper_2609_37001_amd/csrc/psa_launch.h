@@ -43,13 +43,16 @@ struct Geometry {
 constexpr int32_t kDeadTile = -2;
 
 // Identifies a finished plan in the workspace header; the sizes it was made for follow it.
-constexpr uint32_t kPlanMagic = 0x50534131u;  // "PSA1"
-// The same for a plan in which every head keeps every key block (or may, see plan_full), where the
-// engine of a run depends on that.
-constexpr uint32_t kPlanMagicFull = 0x50534132u;
+// Block 64 has a number of its own: "PSA1" plans of it list single query blocks, and a run that took
+// them for pairs would read the pairs of an unwritten section.
+constexpr uint32_t kPlanMagic = 0x50534131u;    // "PSA1"
+constexpr uint32_t kPlanMagic64 = 0x50534132u;  // "PSA2"
+// Set in the magic of a plan in which every head keeps every key block (or may, see plan_full), where
+// the engine of a run depends on that.
+constexpr uint32_t kPlanFull = 0x80000000u;
 
 struct PlanHeader {
-  uint32_t magic;   // kPlanMagic or kPlanMagicFull once the plan's kernels have run, 0 while they run
+  uint32_t magic;   // kPlanMagic*, maybe with kPlanFull, once the plan's kernels have run, 0 while they run
   int32_t n_bh;     // batch * n_heads
   int32_t n_heads;
   int32_t nb;

@@ -89,3 +89,21 @@ def test_full_density_same_bits_as_dense(d, block, grid, heads):
             assert t.equal(o, o2) and t.equal(lse, lse2)
         if params is full:
             assert t.equal(o, dense) and t.equal(lse, dense_lse)
+
+
+@pytest.mark.parametrize("block,magic", [(64, 0x50534131), (128, 0x50534132)])
+@pytest.mark.parametrize("grid", [(4, 8, 128, 0), (16, 8, 128, 0)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_plan_of_another_format_is_left_alone(d, grid, block, magic):
+    """A header that names the right sizes but another kind of plan: nothing is written."""
+    t = gu.torch()
+    n = grid[0] * grid[1] * grid[2]
+    params = [(2, 0, INF, 3, 0, INF)] * 8
+    q = t.ones((1, 8, n, d), device="cuda", dtype=t.bfloat16)
+    ws = psa.plan(params, grid, block)
+    head = ws.tensor.view(t.uint8)[:4]
+    good = head.clone()
+    for want, word in ((0, magic), (n * 8 * d, None)):
+        head.copy_(good if word is None else t.tensor(list(word.to_bytes(4, "little")), dtype=t.uint8))
+        o = psa.run(q, q, q, grid, block, ws, out=t.full_like(q, float("nan")))
+        assert int((~o.isnan()).sum()) == want
