@@ -118,11 +118,11 @@ psa_status_t psa_build_blockmap(const psa_stripe_t* params, int32_t n_heads, psa
  * the stripe parameters of each head to the workspace, counts the kept key blocks of every
  * work item with the Algorithm 1 decoder and orders the items.  A work item is a pair of query
  * blocks of one (batch, head) that share one K/V stream, the pairs formed from query blocks with
- * equal kept sets first (the rest
- * in index order) and weighed by the union of the two sets.  Order: items
- * of more than three times the mean work (rows that keep every key block, such as text rows)
- * first, longest first, then the heads longest first, each split into equal-work ranges, one
- * work queue per XCD.  At block 128 the plan also chooses where each pair item's K/V stream
+ * equal kept sets first (the rest in index order) and weighed by the union of the two sets.  Where
+ * the query blocks are no more than the GPU runs at once, every query block is an item and nothing is
+ * ordered.  Order: short lists longest first; others: items of more than three times the mean work
+ * (rows that keep every key block, such as text rows) first, longest first, then the heads longest first, each split into equal-work ranges, one
+ * work queue per XCD.  At block 128 the plan of a long list also chooses where each item's K/V stream
  * starts (each row still visits each of its kept blocks once, cyclically ascending from there):
  * where the item started just before it on its queue is predicted to be by then, so that the items
  * in flight on one XCD read the same key blocks at about the same time and its L2 serves them
@@ -138,8 +138,8 @@ psa_status_t psa_attention_plan(int32_t batch, int32_t n_heads, psa_grid_t grid,
                                 size_t workspace_bytes, int32_t* kept_per_row,
                                 hipStream_t stream);
 
-/* Sparse attention over a planned workspace (Algorithm 2): one persistent kernel whose
- * workgroups pop work items from the plan's queues, decode the kept key blocks of each query
+/* Sparse attention over a planned workspace (Algorithm 2): a persistent kernel whose
+ * workgroups pop work items from the plan's queues (or one workgroup per query block), decode the kept key blocks of each query
  * block (Algorithm 1) and run the tile engine over them.  Arguments as in psa_attention_fwd.  The
  * workspace must hold a plan made for the same batch, n_heads, grid and block; the kernel checks
  * the plan's header first and, on a mismatch or an unfinished plan, writes nothing (o and lse keep
