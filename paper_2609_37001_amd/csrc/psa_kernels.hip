@@ -2221,10 +2221,10 @@ __device__ __forceinline__ void process_pair(const DmaPlan<D, BLK>& plan, int gr
       const int x = (int)__builtin_amdgcn_readfirstlane(list[j]);
       return SUB == 1 ? x : (x & kEntryBlockMask) * SUB + i % SUB;
     } else {
-      return SUB == 1 ? i | (3 << kEntryRowShift) : i;
+      return i;                             // dense: the block itself, of any number of blocks
     }
   };
-  auto block_of = [](int x) { return SUB == 1 ? x & kEntryBlockMask : x; };
+  auto block_of = [](int x) { return SPARSE && SUB == 1 ? x & kEntryBlockMask : x; };
   // The second half of the sequence's last block may lie past the end altogether; it is loaded
   // from the last half that does not, and masked.
   auto from = [&](int kb) { return SUB == 1 ? kb : min(kb, (n - 1) / BLK); };
@@ -2268,7 +2268,7 @@ __device__ __forceinline__ void process_pair(const DmaPlan<D, BLK>& plan, int gr
   }
   for (int i = 0; i < nu; i++) {
     const int kb = block_of(e);
-    const bool mine = my_row >= 0 && (SUB > 1 || ((e >> (kEntryRowShift + grp)) & 1));
+    const bool mine = my_row >= 0 && (!SPARSE || SUB > 1 || ((e >> (kEntryRowShift + grp)) & 1));
     uint64_t lo = ~0ull, hi = ~0ull;
     bool tail;
     if constexpr (PAD) {
