@@ -207,28 +207,6 @@ psa_status_t check_plan_3d(int32_t batch, int32_t n_heads, psa_grid_t grid, psa_
   return check_work(batch, n_heads, workspace, workspace_bytes, g, wl);
 }
 
-// Whether an axis of `extent` positions keeps every distance: the residues of |delta - offset|, which
-// takes every value of [lo, hi], all lie below the width.
-bool axis_full(int32_t w, int32_t o, int32_t s, int32_t extent) {
-  if (w >= s) return true;
-  const int64_t a = o < 0 ? -(int64_t)o : o, lo = std::max<int64_t>(0, a - (extent - 1)), hi = a + extent - 1;
-  return lo % s + (hi - lo) < w;
-}
-
-// Whether every head keeps every key block.  Never for PSABlocks (their dense counterpart runs on
-// another sequence).  Where a block is longer than a frame not every frame starts one, so stripes
-// that miss only distances no two blocks have would pass for sparse: such grids count as full.
-bool plan_full(const psa::Geometry& g, const psa_stripe_t* params, int32_t n_heads) {
-  if (g.pbt > 0) return false;
-  if (g.block > g.hw) return true;
-  const int32_t slots = (g.hw - 1) / g.block + 1;
-  for (int32_t h = 0; h < n_heads; h++)
-    if (!axis_full(params[h].t_w, params[h].t_o, params[h].t_s, g.frames) ||
-        !axis_full(params[h].s_w, params[h].s_o, params[h].s_s, slots))
-      return false;
-  return true;
-}
-
 // The kernels of a plan over geometry g.
 psa_status_t enqueue_plan(int32_t batch, int32_t n_heads, const psa::Geometry& g,
                           const psa_stripe_t* params, void* workspace,
@@ -237,7 +215,7 @@ psa_status_t enqueue_plan(int32_t batch, int32_t n_heads, const psa::Geometry& g
   psa::ParamChunk chunks[(PSA_MAX_BATCH_HEADS + psa::kHeadsPerChunk - 1) / psa::kHeadsPerChunk];
   for (int32_t h0 = 0; h0 < n_heads; h0 += psa::kHeadsPerChunk)
     chunks[h0 / psa::kHeadsPerChunk] = chunk_of(params, h0, n_heads);
-  const hipError_t e = psa::launch_plan(chunks, g, batch, n_heads, plan_full(g, params, n_heads), workspace, wl,
+  const hipError_t e = psa::launch_plan(chunks, g, batch, n_heads, psa::plan_full(g, params, n_heads), workspace, wl,
                                          kept_per_row, stream);
   return e == hipSuccess ? PSA_OK : hip_fail(e, who);
 }
@@ -278,7 +256,7 @@ psa_status_t run_planned(const void* q, const void* k, const void* v, void* o, i
   const float c = softmax_scale * 1.4426950408889634f;
   hipError_t e = psa::launch_sparse(q, k, v, o, lse, batch, n_heads, head_dim, g, c, workspace, wl,
                                     compute_units(), stream,
-                                    params ? (int32_t)plan_full(g, params, n_heads) : -1);
+                                    params ? (int32_t)psa::plan_full(g, params, n_heads) : -1);
   if (e != hipSuccess) return hip_fail(e, "psa_attention_run kernel launch");
   return PSA_OK;
 }

@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 
 #include "psa.h"
@@ -98,6 +100,36 @@ struct WorkspaceLayout {
 // Query blocks of one head processed together by the pair engine (BLK = 128): ceil(nb / 2)
 // pairs per head, the second member -1 for a single.
 __host__ __device__ inline int32_t pairs_per_head(int32_t nb) { return (nb + 1) / 2; }
+
+// Whether an axis of `extent` positions keeps every distance: the residues of |delta - offset|, which
+// takes every value of [lo, hi], all lie below the width.
+inline bool axis_full(int32_t w, int32_t o, int32_t s, int32_t extent) {
+  if (w >= s) return true;
+  const int64_t a = o < 0 ? -(int64_t)o : o, lo = std::max<int64_t>(0, a - (extent - 1)), hi = a + extent - 1;
+  return lo % s + (hi - lo) < w;
+}
+
+// Whether every head keeps every key block.  Never for PSABlocks (their dense counterpart runs on
+// another sequence).  A head keeps everything if it keeps every distance between two blocks that are
+// not global, on either axis: each such distance belongs to a pair of blocks, which needs both axes.
+// With a block no longer than a frame the coordinates of the n_local blocks before the first global
+// one are whole ranges from zero: every frame up to that of the last of them starts a block, and the
+// first frame's blocks are slots 0, 1, ...  (The text of the first global block may have taken the
+// video's last frame or slot from the map.)  Where a block is longer than a frame not every frame
+// starts one, so stripes that miss only distances no two blocks have would pass for sparse: such
+// grids count as full.
+inline bool plan_full(const Geometry& g, const psa_stripe_t* params, int32_t n_heads) {
+  if (g.pbt > 0) return false;
+  const int32_t n_local = g.n_text > 0 ? g.n_video / g.block : g.nb;
+  if (g.block > g.hw || n_local == 0) return true;
+  const int32_t frames = (int32_t)((int64_t)(n_local - 1) * g.block / g.hw) + 1;
+  const int32_t slots = std::min((g.hw - 1) / g.block + 1, n_local);
+  for (int32_t h = 0; h < n_heads; h++)
+    if (!axis_full(params[h].t_w, params[h].t_o, params[h].t_s, frames) ||
+        !axis_full(params[h].s_w, params[h].s_o, params[h].s_s, slots))
+      return false;
+  return true;
+}
 
 WorkspaceLayout workspace_layout(int32_t batch, int32_t n_heads, int32_t nb, bool masks);
 

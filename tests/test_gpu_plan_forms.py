@@ -91,6 +91,31 @@ def test_full_density_same_bits_as_dense(d, block, grid, heads):
             assert t.equal(o, dense) and t.equal(lse, dense_lse)
 
 
+@pytest.mark.parametrize("grid,stripe,heads", [((1, 30, 52, 226), (1, 0, INF, 12, 0, INF), 24),
+                                               ((1, 10, 20, 100), (1, 0, INF, 1, 0, INF), 100),
+                                               ((1, 3, 43, 1), (1, 0, INF, 1, 0, INF), 150),
+                                               ((2, 10, 20, 30), (1, 0, 2, 2, 0, INF), 70)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_full_by_text_same_bits_as_dense(d, grid, stripe, heads):
+    """Maps that are full only because the text has taken the video's last slot or frame, between the
+    sizes at which the density chooses the engine (257 to 512 blocks of 128); the last is not full."""
+    t = gu.torch()
+    f, h, w, nt = grid
+    n = f * h * w + nt
+    keep = oracle.blockmap([stripe], f, h, w, nt, 128)
+    assert bool(keep.all()) == (f == 1) and 256 < heads * keep.shape[1] <= 512
+    gen = t.Generator(device="cuda").manual_seed(3)
+    q, k, v = (t.randn((1, heads, n, d), generator=gen, device="cuda", dtype=t.bfloat16) for _ in range(3))
+    o, lse = psa.attention_fwd(q, k, v, grid, 128, [stripe] * heads, return_lse=True)
+    o2, lse2 = psa.run(q, k, v, grid, 128, psa.plan([stripe] * heads, grid, 128), return_lse=True)
+    assert t.equal(o, o2) and t.equal(lse, lse2)
+    dense, dense_lse = psa.dense_fwd(q, k, v, 128, return_lse=True)
+    if f == 1:
+        assert t.equal(o, dense) and t.equal(lse, dense_lse)
+    else:
+        assert not t.equal(lse, dense_lse)
+
+
 @pytest.mark.parametrize("block,magic", [(64, 0x50534131), (128, 0x50534132)])
 @pytest.mark.parametrize("grid", [(4, 8, 128, 0), (16, 8, 128, 0)])
 @pytest.mark.parametrize("d", [64, 128])
