@@ -2721,23 +2721,30 @@ static hipError_t launch_dense_t(const void* q, const void* k, const void* v, vo
                                  int32_t n_bh, int32_t n, float c, int32_t* queues, int32_t cus,
                                  hipStream_t stream) {
   PlanHeader e = {};
-  e.n_bh = n_bh;
-  e.n_heads = n_bh;
   e.nb = (n + BLK * SUB - 1) / (BLK * SUB);
   e.n = n;
-  const int32_t n_items = n_bh * pairs_per_head(e.nb);
-  const int32_t per_xcd = (n_items * SUB + kNumQueues - 1) / kNumQueues;
+  const int32_t np = pairs_per_head(e.nb);
   if (queues) {
-    hipLaunchKernelGGL(psa_dense_arm_kernel, dim3(1), dim3(64), 0, stream, queues, n_items);
+    hipLaunchKernelGGL(psa_dense_arm_kernel, dim3(1), dim3(64), 0, stream, queues, n_bh * np);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
-  const int32_t grid = queues ? pair_grid<D, BLK>(cus, n_items * SUB, 0) : per_xcd * kNumQueues;
   const PlanView pv = {0, 0, 0, 0, 0, 0, 0};      // the dense workspace is the queue area
-  hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, false, false>), dim3(grid), dim3(4 * BLK), 0, stream,
-                     (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse,
-                     (const uint8_t*)queues, pv, e, c);
-  return hipGetLastError();
+  // A launch takes fewer than 2^32 threads: with one workgroup per item, as many heads at a time.
+  constexpr int32_t kItems = (int32_t)((((int64_t)1 << 32) - 1) / (4 * BLK) / SUB - kNumQueues);
+  const int32_t slice = queues ? n_bh : max(1, min(n_bh, kItems / np));
+  for (int32_t bh = 0; bh < n_bh; bh += slice) {
+    e.n_bh = e.n_heads = min(slice, n_bh - bh);
+    const int32_t n_items = e.n_bh * np, per_xcd = (n_items * SUB + kNumQueues - 1) / kNumQueues;
+    const int32_t grid = queues ? pair_grid<D, BLK>(cus, n_items * SUB, 0) : per_xcd * kNumQueues;
+    const size_t off = (size_t)bh * n * D;
+    hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, false, false>), dim3(grid), dim3(4 * BLK), 0, stream,
+                       (const __bf16*)q + off, (const __bf16*)k + off, (const __bf16*)v + off, (__bf16*)o + off,
+                       lse ? lse + (size_t)bh * n : nullptr, (const uint8_t*)queues, pv, e, c);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, float* lse,

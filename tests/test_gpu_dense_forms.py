@@ -1,5 +1,5 @@
 """Dense attention at the ends of its range: more key blocks than an entry of the sparse key list can
-number."""
+number, more heads than one launch can take."""
 import math
 
 import numpy as np
@@ -29,3 +29,18 @@ def test_more_blocks_than_a_list_entry_numbers(d, block):
     want = math.log(n - extra + extra * 2.0 ** s)
     assert float((lse - want).abs().max()) <= gu.LSE_ABS_TOL
     assert float((o.float() - 1.0).abs().max()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_more_heads_than_one_launch_takes(d):
+    """One workgroup per item (no workspace) and 2^24 + 3 heads of one token: of 256 threads each they
+    are more than the 2^32 - 1 threads of a launch.  The only key has weight 1, so o = v and the
+    normaliser is the score."""
+    t = gu.torch()
+    heads = 2 ** 24 + 3
+    q = t.full((1, heads, 1, d), 0.5, device="cuda", dtype=t.bfloat16)
+    v = t.randn(q.shape, device="cuda", dtype=t.bfloat16, generator=t.Generator(device="cuda").manual_seed(2))
+    o, lse = psa.dense_fwd(q, q, v, 64, 0.125, return_lse=True, balanced=False, out=t.full_like(v, float("nan")))
+    assert t.equal(o, v)
+    s = 0.5 * d * float(gu.kernel_q(np.full(1, 0.5), 0.125)[0]) * math.log(2.0)
+    assert float((lse - s).abs().max()) <= 1e-5
