@@ -200,8 +200,9 @@ size_t psa_dense_workspace_size(void);
  *                  With a workspace a small kernel arms per-XCD work queues in it and a
  *                  persistent grid takes the work items, each workgroup from its own XCD's queue
  *                  first and then from the others, so XCDs that run at different clocks finish
- *                  together.  Without one, each XCD gets an equal fixed share.  The output is
- *                  the same bits either way.  Calls sharing a workspace must not overlap in time.
+ *                  together.  Without one, and for calls too small for queues to pay (few query
+ *                  blocks, or sequences of at most 512 tokens), each XCD gets an equal fixed share.
+ *                  The output is the same bits either way.  Calls sharing a workspace must not overlap in time.
  * A workspace that is too small or misaligned is rejected with PSA_ERR_WORKSPACE. */
 psa_status_t psa_dense_fwd(const void* q, const void* k, const void* v, void* o, int32_t batch,
                            int32_t n_heads, int32_t head_dim, int32_t n_tokens, int32_t block,

@@ -2065,6 +2065,8 @@ __global__ __launch_bounds__(64) void psa_rearm_kernel(int32_t* __restrict__ que
 //     (SUB = 2): a work item of the plan's pairs is two parts, one query block each, whose halves
 //     are the two groups' rows and whose 128-key blocks are two entries of 64 keys.  60 heads x
 //     17776 tokens: 1.55 ms with eight waves and two waves per SIMD, 1.44 ms this way.
+//   * head dim 64, block 128, eight waves: one workgroup per CU (two waves per SIMD at 160 registers;
+//     four need 128 and spill 40, 1.5 times as long), for dense calls of few items (launch_dense).
 // ---------------------------------------------------------------------------------------------
 
 // Direct global->LDS loads of a whole K or V block by the waves of a workgroup: wave w
@@ -2338,7 +2340,7 @@ struct PlanView {
 // gives.  See the shapes above.
 template <int D, int BLK>
 struct PairShape {
-  static constexpr int kWavesPerSimd = D == 64 ? 4 : 2;
+  static constexpr int kWavesPerSimd = D == 64 && BLK == 64 ? 4 : 2;
   static constexpr int kPerCu = kWavesPerSimd * 64 / BLK;
 };
 
@@ -2712,16 +2714,15 @@ hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, f
 }
 
 // Dense attention.  With queues (a dense workspace) a one-thread-group kernel arms them and a
-// persistent grid takes the items; without, one workgroup per item.  The items are pairs of
-// 128-row blocks at either block size: every block is kept, so the block size changes neither the
-// keys of a row nor their order, and both give the same bits.  (Few query blocks run on the split
-// engine, which reads no queues.)
-template <int D, int BLK, int SUB>
+// persistent grid takes the items; without, one workgroup per item.  The items are pairs of BLK-row
+// blocks; every block is kept, so BLK changes neither the keys of a row nor their order, and all
+// shapes give the same bits.
+template <int D, int BLK>
 static hipError_t launch_dense_t(const void* q, const void* k, const void* v, void* o, float* lse,
                                  int32_t n_bh, int32_t n, float c, int32_t* queues, int32_t cus,
                                  hipStream_t stream) {
   PlanHeader e = {};
-  e.nb = (n + BLK * SUB - 1) / (BLK * SUB);
+  e.nb = (n + BLK - 1) / BLK;
   e.n = n;
   const int32_t np = pairs_per_head(e.nb);
   if (queues) {
@@ -2731,14 +2732,14 @@ static hipError_t launch_dense_t(const void* q, const void* k, const void* v, vo
   }
   const PlanView pv = {0, 0, 0, 0, 0, 0, 0};      // the dense workspace is the queue area
   // A launch takes fewer than 2^32 threads: with one workgroup per item, as many heads at a time.
-  constexpr int32_t kItems = (int32_t)((((int64_t)1 << 32) - 1) / (4 * BLK) / SUB - kNumQueues);
+  constexpr int32_t kItems = (int32_t)((((int64_t)1 << 32) - 1) / (4 * BLK) - kNumQueues);
   const int32_t slice = queues ? n_bh : max(1, min(n_bh, kItems / np));
   for (int32_t bh = 0; bh < n_bh; bh += slice) {
     e.n_bh = e.n_heads = min(slice, n_bh - bh);
-    const int32_t n_items = e.n_bh * np, per_xcd = (n_items * SUB + kNumQueues - 1) / kNumQueues;
-    const int32_t grid = queues ? pair_grid<D, BLK>(cus, n_items * SUB, 0) : per_xcd * kNumQueues;
+    const int32_t n_items = e.n_bh * np, per_xcd = (n_items + kNumQueues - 1) / kNumQueues;
+    const int32_t grid = queues ? pair_grid<D, BLK>(cus, n_items, 0) : per_xcd * kNumQueues;
     const size_t off = (size_t)bh * n * D;
-    hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, false, false>), dim3(grid), dim3(4 * BLK), 0, stream,
+    hipLaunchKernelGGL((psa_pair_kernel<D, BLK, 1, false, false>), dim3(grid), dim3(4 * BLK), 0, stream,
                        (const __bf16*)q + off, (const __bf16*)k + off, (const __bf16*)v + off, (__bf16*)o + off,
                        lse ? lse + (size_t)bh * n : nullptr, (const uint8_t*)queues, pv, e, c);
     const hipError_t err = hipGetLastError();
@@ -2746,6 +2747,9 @@ static hipError_t launch_dense_t(const void* q, const void* k, const void* v, vo
   }
   return hipSuccess;
 }
+
+// Longest sequence of the short dense calls below.
+constexpr int32_t kDenseShort = 512;
 
 hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, float* lse,
                         int32_t batch, int32_t n_heads, int32_t head_dim, int32_t n_tokens,
@@ -2767,10 +2771,27 @@ hipError_t launch_dense(const void* q, const void* k, const void* v, void* o, fl
       return head_dim == 128 ? go(psa_split_kernel<128, 128, false, false>) : go(psa_split_kernel<64, 128, false, false>);
     return head_dim == 128 ? go(psa_split_kernel<128, 64, false, false>) : go(psa_split_kernel<64, 64, false, false>);
   }
+  // Short sequences take 64-row pairs and a fixed grid: of a 128-row pair half and more would lie past
+  // their end, and a pop of the queues costs as much as their items.  Heads x tokens, 128-row pairs
+  // and queues -> this: head dim 64 4096 x 64 123 -> 28 us, 4096 x 256 197 -> 141, 4096 x 512 419 ->
+  // 374; head dim 128 4096 x 64 105 -> 58, 4096 x 256 273 -> 260, 4096 x 512 739 -> 733, 128 x 384
+  // 22.5 -> 19.3.  On longer ones 128-row pairs read K and V half as often (3 to 10 % faster at head
+  // dim 128), and the queues level the XCDs.
+  if (n_tokens <= kDenseShort) {
+    if (head_dim == 128) return launch_dense_t<128, 64>(q, k, v, o, lse, n_bh, n_tokens, c, nullptr, cus, stream);
+    if (head_dim == 64) return launch_dense_t<64, 64>(q, k, v, o, lse, n_bh, n_tokens, c, nullptr, cus, stream);
+    return hipErrorInvalidValue;
+  }
   if (head_dim == 128)
-    return launch_dense_t<128, 128, 1>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
-  if (head_dim == 64)
-    return launch_dense_t<64, 64, 2>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
+    return launch_dense_t<128, 128>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
+  if (head_dim == 64) {
+    // No more 256-row items than CUs: one round of them at two waves per SIMD, where the four-wave
+    // shape's 128-row items fill the CUs unevenly (48 heads x 1024 tokens 27.4 -> 24.1 us, 12 x 3600
+    // 71 -> 61, 6 x 7800 141 -> 117; beyond the line 128 x 768 would take 37.6 against 31.8).
+    if ((int64_t)n_bh * pairs_per_head((n_tokens + 127) / 128) <= cus)
+      return launch_dense_t<64, 128>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
+    return launch_dense_t<64, 64>(q, k, v, o, lse, n_bh, n_tokens, c, queues, cus, stream);
+  }
   return hipErrorInvalidValue;
 }
 
