@@ -1537,26 +1537,6 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   return h;
 }
 
-// Which problems run on the split engine, by their query blocks; the lines are for the 256 CUs of an
-// MI355X (fixed numbers: a plan and its runs have to agree).
-//  * Up to one workgroup per CU (at block 64, two of the half as large ones): always.
-//  * Up to two: unless every head keeps every key block.  Rows of unequal length gain 1.0 to 1.75
-//    times over pairs (28 drawn calls: 1.08 in the mean), because the longest pair sets the time;
-//    rows of equal length lose up to 13 %, two rounds of half the work and more for one.  The dense
-//    path therefore stays on pairs, and so does the sparse path at full density, where it returns
-//    the dense path's bits.
-//    Beyond two the longest-first list of pairs is 2 % faster in the mean (24 drawn calls).
-static bool split_any(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 256 * (128 / block); }
-static bool split_sparse(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 512 * (128 / block); }
-// Whether the density decides; such a plan's header says which it is (kPlanFull).
-static bool split_by_density(int32_t n_bh, int32_t nb, int32_t block) {
-  return split_sparse(n_bh, nb, block) && !split_any(n_bh, nb, block);
-}
-// Whether no run of this plan needs pairs.
-static bool split_plan(int32_t n_bh, int32_t nb, int32_t block, bool full) {
-  return split_any(n_bh, nb, block) || (!full && split_sparse(n_bh, nb, block));
-}
-
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
 static bool has_starts(const Geometry& g) { return g.block == 128; }
 

@@ -131,6 +131,30 @@ inline bool plan_full(const Geometry& g, const psa_stripe_t* params, int32_t n_h
   return true;
 }
 
+// Which problems run on the split engine, by their query blocks; the lines are for the 256 CUs of an
+// MI355X (fixed numbers: a plan and its runs have to agree).
+//  * Up to one workgroup per CU (at block 64, two of the half as large ones): always.
+//  * Up to two: unless every head keeps every key block.  Rows of unequal length gain 1.0 to 1.75
+//    times over pairs (28 drawn calls: 1.08 in the mean), because the longest pair sets the time;
+//    rows of equal length lose up to 13 %, two rounds of half the work and more for one.  The dense
+//    path therefore stays on pairs, and so does the sparse path at full density, where it returns
+//    the dense path's bits.  At block 128 also not with two to eight blocks per head, whose rows
+//    differ by little (head dim 128: 200 heads x 256 tokens 22.1 us split and 18.2 in pairs, 128 x 512
+//    28.8 and 24.7, 64 x 1024 35.4 and 31.2; but 40 x 1280 31.9 and 32.7, 25 x 2048 39.1 and 47.9).
+//    Beyond two the longest-first list of pairs is 2 % faster in the mean (24 drawn calls).
+inline bool split_any(int32_t n_bh, int32_t nb, int32_t block) { return n_bh * nb <= 256 * (128 / block); }
+inline bool split_sparse(int32_t n_bh, int32_t nb, int32_t block) {
+  return split_any(n_bh, nb, block) || (n_bh * nb <= 512 * (128 / block) && (block == 64 || nb == 1 || nb > 8));
+}
+// Whether the density decides; such a plan's header says which it is (kPlanFull).
+inline bool split_by_density(int32_t n_bh, int32_t nb, int32_t block) {
+  return split_sparse(n_bh, nb, block) && !split_any(n_bh, nb, block);
+}
+// Whether no run of this plan needs pairs.
+inline bool split_plan(int32_t n_bh, int32_t nb, int32_t block, bool full) {
+  return split_any(n_bh, nb, block) || (!full && split_sparse(n_bh, nb, block));
+}
+
 WorkspaceLayout workspace_layout(int32_t batch, int32_t n_heads, int32_t nb, bool masks);
 
 // Launchers; each returns the hipError_t of its launch(es).

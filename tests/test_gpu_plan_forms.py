@@ -28,11 +28,13 @@ def stripes(heads, f, sp, seed):
 
 # batch, heads, (F, H, W, text), block, head_dim.  The first lines are the sizes at which a call changes
 # between the split engine (up to 256 query blocks, 512 unless every head keeps every block; twice as
-# many at block 64) and the pair engine.
+# many at block 64, and at block 128 only with one or more than eight blocks per head beyond 256) and
+# the pair engine.
 CASES = [(1, 4, (4, 8, 256, 0), 128, 128), (1, 4, (4, 8, 256, 1), 128, 128), (1, 4, (8, 8, 256, 0), 128, 64),
          (1, 4, (8, 8, 256, 1), 128, 64), (2, 4, (4, 8, 128, 0), 64, 64), (2, 4, (4, 8, 128, 2), 64, 128),
          (2, 4, (8, 8, 128, 0), 64, 128), (2, 4, (8, 8, 128, 3), 64, 64), (1, 1, (64, 8, 128, 0), 64, 64),
          (1, 1, (64, 8, 128, 0), 128, 128),
+         (1, 64, (1, 8, 128, 0), 128, 128), (1, 56, (1, 8, 144, 0), 128, 128), (1, 200, (1, 8, 32, 0), 128, 64),
          (1, 1, (1, 1, 7, 0), 64, 64), (2, 3, (1, 8, 16, 0), 128, 128), (1, 3, (2, 8, 16, 5), 128, 64),
          (1, 4, (16, 8, 128, 0), 128, 128), (1, 4, (16, 8, 128, 1), 128, 128), (2, 4, (16, 8, 64, 0), 64, 128),
          (1, 64, (3, 8, 24, 3), 64, 64), (2, 65, (3, 8, 24, 3), 64, 64), (1, 65, (3, 4, 11, 0), 128, 128),
