@@ -1075,6 +1075,7 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   }
   __syncthreads();
   if (tid == 0) {
+    done.halves = done.halves && halves_pay(total - kItemOverhead * n, mx, n);
     __threadfence();
     *header = done;
   }
@@ -1344,7 +1345,11 @@ __global__ __launch_bounds__(1024) void psa_schedule_kernel(const int32_t* __res
   }
   if (tid <= kNumQueues) queues[tid] = qstart[tid];
   if (tid < kNumQueues) queues[kQueueCounters + tid * kCounterStride] = 0;
-  if (tid == 0) queues[kStartsDone] = 0;
+  if (tid == 0) {
+    done.halves = done.halves && halves_pay((int64_t)all_work - (int64_t)kItemOverhead * n, max_count, n);
+    queues[kStartsDone] = 0;
+    queues[kHalvesWord] = done.halves;
+  }
   __syncthreads();
   if (tid == 0 && write_header) {
     __threadfence();
@@ -1514,6 +1519,7 @@ __global__ __launch_bounds__(1024) void psa_starts_kernel(
     __threadfence();
     if (atomicAdd(&queues[kStartsDone], 1) == kNumQueues - 1) {
       __threadfence();
+      done.halves = queues[kHalvesWord];
       *header = done;
     }
   }
@@ -1534,6 +1540,7 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   h.pbt = g.pbt;
   h.pbh = g.pbh;
   h.pbw = g.pbw;
+  h.halves = 0;
   return h;
 }
 
@@ -1565,6 +1572,7 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const bool split = split_plan(batch * n_heads, g.nb, g.block, full);
   PlanHeader done = plan_header(g, batch, n_heads);
   if (split_by_density(batch * n_heads, g.nb, g.block) && full) done.magic |= kPlanFull;
+  done.halves = halves_possible(g.block, n_items, g.nb);      // narrowed by the work the kernels count
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -2041,12 +2049,13 @@ __global__ __launch_bounds__(64) void psa_rearm_kernel(int32_t* __restrict__ que
 //   * head dim 64: half the MFMA work per score for the same softmax, so the VALU bounds it and
 //     waves matter more than registers: four per SIMD (128 registers each, 32 KB + list per
 //     workgroup).  32 heads x 17776 tokens, block 64: 1.57 ms with one wave per SIMD, 0.95 with
-//     two, 0.90 with three, 0.85 with four.  Block 128 runs on the same four-wave workgroups
-//     (SUB = 2): a work item of the plan's pairs is two parts, one query block each, whose halves
-//     are the two groups' rows and whose 128-key blocks are two entries of 64 keys.  60 heads x
-//     17776 tokens: 1.55 ms with eight waves and two waves per SIMD, 1.44 ms this way.
-//   * head dim 64, block 128, eight waves: one workgroup per CU (two waves per SIMD at 160 registers;
-//     four need 128 and spill 40, 1.5 times as long), for dense calls of few items (launch_dense).
+//     two, 0.90 with three, 0.85 with four.  Where there is enough work per CU (halves_pay) block
+//     128 runs on the same four-wave workgroups (SUB = 2): a work item of the plan's pairs is two
+//     parts, one query block each, whose halves are the two groups' rows and whose 128-key blocks
+//     are two entries of 64 keys.
+//   * head dim 64, block 128, eight waves: one workgroup per CU (two waves per SIMD at 167 registers;
+//     four waves mean 128 and spill 37, 1.5 times as long), where there is not, and for dense calls of
+//     few items (launch_dense).
 // ---------------------------------------------------------------------------------------------
 
 // Direct global->LDS loads of a whole K or V block by the waves of a workgroup: wave w
@@ -2352,6 +2361,8 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
   if constexpr (SPARSE) {
     // A workspace without a finished plan for exactly these sizes is left alone.
     if (!plan_matches(*header, expect)) return;
+    // Of the two shapes of head dim 64 at block 128 the plan has chosen one.
+    if (D == 64 && BLK * SUB == 128 && (header->halves != 0) != (SUB == 2)) return;
   }
   const int32_t n_heads = expect.n_heads, n = expect.n, nb = expect.nb;
   const int32_t np = pairs_per_head(nb), n_items = expect.n_bh * np;
@@ -2630,6 +2641,18 @@ static int32_t pair_grid(int32_t cus, int32_t n_items, int32_t list_bytes) {
 }
 
 template <int D, int BLK, int SUB, bool PAD>
+static hipError_t launch_pairs(const void* q, const void* k, const void* v, void* o, float* lse,
+                               const PlanHeader& expect, float c, const char* ws, const PlanView& pv, int32_t cus,
+                               hipStream_t stream) {
+  const int32_t list_bytes = D == 64 ? (2 * expect.nb + 15) & ~15 : 0;
+  const int32_t grid = pair_grid<D, BLK>(cus, expect.n_bh * pairs_per_head(expect.nb) * SUB, list_bytes);
+  hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, true, PAD>), dim3(grid), dim3(4 * BLK), list_bytes, stream,
+                     (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse,
+                     (const uint8_t*)ws, pv, expect, c);
+  return hipGetLastError();
+}
+
+template <int D, int BLOCK, bool PAD>
 static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, void* o,
                                   float* lse, const PlanHeader& sizes, float c,
                                   void* workspace, const WorkspaceLayout& wl, int32_t cus,
@@ -2640,11 +2663,11 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
                        (uint32_t)(PAD ? wl.masks : 0), (uint32_t)wl.pairs, (uint32_t)wl.starts};
   PlanHeader expect = sizes;
   bool rearm = full < 0;
-  const bool by_density = split_by_density(expect.n_bh, expect.nb, BLK * SUB);
-  if (split_any(expect.n_bh, expect.nb, BLK * SUB) || (by_density && full != 1)) {
-    hipLaunchKernelGGL((psa_split_kernel<D, BLK * SUB, true, PAD>), dim3(expect.n_bh * expect.nb),
-                       dim3(4 * BLK * SUB), 0, stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v,
-                       (__bf16*)o, lse, (const uint8_t*)ws, pv, expect, c);
+  const bool by_density = split_by_density(expect.n_bh, expect.nb, BLOCK);
+  if (split_any(expect.n_bh, expect.nb, BLOCK) || (by_density && full != 1)) {
+    hipLaunchKernelGGL((psa_split_kernel<D, BLOCK, true, PAD>), dim3(expect.n_bh * expect.nb), dim3(4 * BLOCK), 0,
+                       stream, (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse,
+                       (const uint8_t*)ws, pv, expect, c);
     const hipError_t e = hipGetLastError();
     // Of a run, whose plan's density only the device knows, both engines are launched where it
     // decides, and the one that does not fit the plan returns at once (PSABlock plans are never full).
@@ -2658,12 +2681,31 @@ static hipError_t launch_sparse_t(const void* q, const void* k, const void* v, v
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  const int32_t list_bytes = D == 64 ? (2 * expect.nb + 15) & ~15 : 0;
-  const int32_t grid = pair_grid<D, BLK>(cus, expect.n_bh * pairs_per_head(expect.nb) * SUB, list_bytes);
-  hipLaunchKernelGGL((psa_pair_kernel<D, BLK, SUB, true, PAD>), dim3(grid), dim3(4 * BLK), list_bytes, stream,
-                     (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse,
-                     (const uint8_t*)ws, pv, expect, c);
-  return hipGetLastError();
+  if constexpr (D == 64 && BLOCK == 128) {
+    // The plan's work decides, which only the device knows: where the sizes leave it open both shapes
+    // are launched, and the other one returns at once.
+    const hipError_t e = launch_pairs<64, 128, 1, PAD>(q, k, v, o, lse, expect, c, ws, pv, cus, stream);
+    if (e != hipSuccess || !halves_possible(BLOCK, (int64_t)expect.n_bh * pairs_per_head(expect.nb), expect.nb))
+      return e;
+    return launch_pairs<64, 64, 2, PAD>(q, k, v, o, lse, expect, c, ws, pv, cus, stream);
+  } else {
+    return launch_pairs<D, BLOCK, 1, PAD>(q, k, v, o, lse, expect, c, ws, pv, cus, stream);
+  }
+}
+
+template <bool PAD>
+static hipError_t launch_sparse_pad(const void* q, const void* k, const void* v, void* o, float* lse,
+                                    int32_t head_dim, int32_t block, const PlanHeader& e, float c, void* workspace,
+                                    const WorkspaceLayout& wl, int32_t cus, hipStream_t stream, int32_t full) {
+  if (head_dim == 128 && block == 128)
+    return launch_sparse_t<128, 128, PAD>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
+  if (head_dim == 64 && block == 64)
+    return launch_sparse_t<64, 64, PAD>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
+  if (head_dim == 128 && block == 64)
+    return launch_sparse_t<128, 64, PAD>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
+  if (head_dim == 64 && block == 128)
+    return launch_sparse_t<64, 128, PAD>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, float* lse,
@@ -2671,26 +2713,8 @@ hipError_t launch_sparse(const void* q, const void* k, const void* v, void* o, f
                          float c, void* workspace, const WorkspaceLayout& wl, int32_t cus,
                          hipStream_t stream, int32_t full) {
   const PlanHeader e = plan_header(g, batch, n_heads);
-  if (g.pbt > 0) {
-    if (head_dim == 128 && g.block == 128)
-      return launch_sparse_t<128, 128, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-    if (head_dim == 64 && g.block == 64)
-      return launch_sparse_t<64, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-    if (head_dim == 128 && g.block == 64)
-      return launch_sparse_t<128, 64, 1, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-    if (head_dim == 64 && g.block == 128)
-      return launch_sparse_t<64, 64, 2, true>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-    return hipErrorInvalidValue;
-  }
-  if (head_dim == 128 && g.block == 128)
-    return launch_sparse_t<128, 128, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-  if (head_dim == 64 && g.block == 64)
-    return launch_sparse_t<64, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-  if (head_dim == 128 && g.block == 64)
-    return launch_sparse_t<128, 64, 1, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-  if (head_dim == 64 && g.block == 128)
-    return launch_sparse_t<64, 64, 2, false>(q, k, v, o, lse, e, c, workspace, wl, cus, stream, full);
-  return hipErrorInvalidValue;
+  return g.pbt > 0 ? launch_sparse_pad<true>(q, k, v, o, lse, head_dim, g.block, e, c, workspace, wl, cus, stream, full)
+                   : launch_sparse_pad<false>(q, k, v, o, lse, head_dim, g.block, e, c, workspace, wl, cus, stream, full);
 }
 
 // Dense attention.  With queues (a dense workspace) a one-thread-group kernel arms them and a

@@ -62,6 +62,8 @@ struct PlanHeader {
   int32_t n;
   int32_t frames, height, width, n_text;
   int32_t pbt, pbh, pbw;
+  int32_t halves;   // whether runs of head dim 64 at block 128 take each pair as two items (set by the
+                    // plan; not one of the sizes a run compares)
 };
 
 // Layout of the queue area (int32 words): kNumQueues + 1 boundaries in the first 128-byte line,
@@ -73,7 +75,9 @@ constexpr int kQueueWords = kQueueCounters + kNumQueues * kCounterStride;
 // Word of the first line (after the boundaries) counting the finished workgroups of the plan's
 // last kernel (psa_starts_kernel).
 constexpr int kStartsDone = 16;
-static_assert(kStartsDone > kNumQueues && kStartsDone < kQueueCounters, "free word of the first line");
+// Another one holding PlanHeader::halves until that kernel writes the header.
+constexpr int kHalvesWord = 17;
+static_assert(kStartsDone > kNumQueues && kHalvesWord < kQueueCounters, "free words of the first line");
 
 // Workspace of psa_dense_fwd: the queue area alone, rounded up to 256 bytes.
 constexpr size_t kDenseWorkspaceBytes = (sizeof(int32_t) * kQueueWords + 255) / 256 * 256;
@@ -153,6 +157,28 @@ inline bool split_by_density(int32_t n_bh, int32_t nb, int32_t block) {
 // Whether no run of this plan needs pairs.
 inline bool split_plan(int32_t n_bh, int32_t nb, int32_t block, bool full) {
   return split_any(n_bh, nb, block) || (!full && split_sparse(n_bh, nb, block));
+}
+
+// Head dim 64 at block 128: whether a run takes every pair of query blocks as two items of one block
+// each, on four-wave workgroups, four to a CU (psa_pair_kernel<64, 64, 2>), or as one item on an
+// eight-wave one, one to a CU (<64, 128, 1>).  Four workgroups per CU hide more latency, but an item
+// that outlasts the others of its CU then runs on at one wave per SIMD, and every block streams K and
+// V for itself.  Two items pay where a CU's share of the work is at least 1.4 times the longest pair
+// and pairs keep six blocks or more in the mean: of the lines tried (0.8 to 2.5 times, 3 to 12 blocks)
+// the one with the best mean over 201 calls of 2 to 591 blocks per head at densities of 0.05 to 1.
+// There it is 1.08 times as fast as one item always with the order by heads, the slowest call 0.94;
+// two items always are 1.04, the slowest 0.75.  One item and two: 12 heads x 17776 tokens at density
+// 0.25 297 and 356 us, 16 x 7800 84 and 103; 60 x 17776 1414 and 1322, 24 x 3600 at density 1 126 and
+// 107.
+// `work` and `longest` count kept key blocks over the plan's n_items pairs.
+constexpr int64_t kHalvesShare = 7 * 256, kHalvesUnit = 5;     // 1.4 times the longest, on each of 256 CUs
+constexpr int32_t kHalvesMean = 6;
+__host__ __device__ inline bool halves_pay(int64_t work, int64_t longest, int64_t n_items) {
+  return work * kHalvesUnit >= kHalvesShare * longest && work >= kHalvesMean * n_items;
+}
+// Whether any plan of these sizes can pass that line (every item keeping every block).
+inline bool halves_possible(int32_t block, int64_t n_items, int32_t nb) {
+  return block == 128 && halves_pay(n_items * nb, nb, n_items);
 }
 
 WorkspaceLayout workspace_layout(int32_t batch, int32_t n_heads, int32_t nb, bool masks);

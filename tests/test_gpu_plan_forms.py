@@ -118,6 +118,55 @@ def test_full_by_text_same_bits_as_dense(d, grid, stripe, heads):
         assert not t.equal(lse, dense_lse)
 
 
+HALVES_WORD = 13                                # of the plan header, after the sizes
+
+
+@pytest.mark.parametrize("pb", [None, (2, 8, 8), (1, 8, 32)])
+@pytest.mark.parametrize("nt,text_rows", [(0, False), (65, False), (130, True)])
+def test_both_shapes_of_head_dim_64_give_the_same_bits(pb, nt, text_rows):
+    """At head dim 64 and block 128 the plan chooses between one item and two per pair; a run does what
+    its header says, on either layout, with the same bits, and some heads are compared with the oracle.
+    The long rows of text at low density choose one item, full rows two."""
+    t = gu.torch()
+    f, h, w, d, heads = 5, 14, 45, 64, 40
+    n, grid = f * h * w + nt, (f, h, w, nt)
+    rng = np.random.default_rng([23, nt, 0 if pb is None else pb[0]])
+    tp, sp = (f, -(-(h * w) // 128)) if pb is None else (-(-f // pb[0]), -(-h // pb[1]) * -(-w // pb[2]))
+    if text_rows:
+        params = [(1, 0, INF, 1, 0, INF)] * heads
+    else:
+        params = [(tp, 0, INF, sp, 0, INF) if i % 4 else (int(rng.integers(1, tp + 1)), int(rng.integers(-1, 2)), 3,
+                                                         int(rng.integers(1, sp + 1)), 0, 5) for i in range(heads)]
+    gen = t.Generator(device="cuda").manual_seed(nt + 1)
+    q, k, v = (t.randn((1, heads, n, d), generator=gen, device="cuda", dtype=t.bfloat16) for _ in range(3))
+    if pb is None:
+        ws = psa.plan(params, grid, 128)
+        go = lambda: psa.run(q, k, v, grid, 128, ws, 0.1, return_lse=True, out=t.full_like(q, float("nan")))
+    else:
+        ws = psa.plan_3d(params, grid, pb, 128)
+        qb, kb, vb = (psa.to_blocks(x, grid, pb) for x in (q, k, v))
+
+        def go():
+            o, lse = psa.run_3d(qb, kb, vb, grid, pb, 128, ws, 0.1, return_lse=True, out=t.full_like(qb, float("nan")))
+            lse = t.stack([t.from_numpy(oracle.from_blocks(lse[0, i].cpu().numpy()[:, None], f, h, w, nt, pb)[:, 0])
+                           for i in range(heads)])[None]
+            return psa.from_blocks(o, grid, pb), lse
+    word = ws.tensor.view(t.int32)[HALVES_WORD:HALVES_WORD + 1]
+    assert int(word) == (0 if text_rows else 1)
+    o, lse = go()
+    word.fill_(1 - int(word))
+    o2, lse2 = go()
+    assert t.equal(o, o2) and t.equal(lse, lse2)
+    pick = [0, 1, heads - 1]
+    host = lambda x: x[:, pick].float().cpu().numpy()
+    if pb is None:
+        keep, groups = oracle.blockmap(params, f, h, w, nt, 128), None
+    else:
+        keep, groups = oracle.psablock_map(params, f, h, w, nt, pb), oracle.token_groups(f, h, w, nt, pb)
+    gu.compare_all(host(q), host(k), host(v), keep[pick], 128, 0.1, host(o), lse[:, pick].cpu().numpy(),
+                   groups=groups).check("pb %s, %d text:" % (pb, nt))
+
+
 @pytest.mark.parametrize("block,magic", [(64, 0x50534131), (128, 0x50534132)])
 @pytest.mark.parametrize("grid", [(4, 8, 128, 0), (16, 8, 128, 0)])
 @pytest.mark.parametrize("d", [64, 128])
