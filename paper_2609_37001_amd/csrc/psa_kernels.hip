@@ -958,15 +958,25 @@ constexpr int kScheduleWaves = 16;
 // per workgroup) 1333 -> 982 us, 10 heads of 28875 (4.4) 2204 -> 1910 us; at 12 items per workgroup
 // and more the order by heads is 1 to 4 % faster, because the workgroups of an XCD then read the
 // same key blocks at about the same time.
+// With `whole`, heads of a few items go to one queue whole, ranked by their mean work: the items of a
+// head then run one after the other on one XCD, whose L2 serves K and V once.  Spread over the queues
+// they are read by several XCDs at different times, which cost lists of more than three items per CU
+// up to 8 % (256 heads x 1024 tokens of head dim 128 77.8 us, whole 71.8, in the order by heads 71.4;
+// block 64, 512 x 512 72 and 65, head dim 64 1024 x 512 95 and 86).  Shorter lists and fewer heads than
+// CUs are a matter of balance, where whole heads lose 1 to 4 %.
 // One workgroup; a wave owns a contiguous slice of the items, 64 cw of them, 64 at a time.
 constexpr int kRankItems = 16384;
 constexpr int kRankClasses = 64;
+constexpr int kWholeHead = 5;             // items of a head that goes whole ...
+constexpr int kWholeItems = 768;          // ... in a list of more than this many items
+constexpr int kWholeHeads = 256;          // ... of at least this many heads
 __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restrict__ counts,
                                                         int32_t* __restrict__ order,
                                                         int32_t* __restrict__ queues,
                                                         int32_t* __restrict__ starts,
                                                         PlanHeader* __restrict__ header,
-                                                        PlanHeader done, int32_t per_head) {
+                                                        PlanHeader done, int32_t per_head,
+                                                        int32_t whole) {
   constexpr int C = kRankItems / 1024, kBins = kNumQueues * kRankClasses;
   static_assert(kBins <= 1024, "a thread per bin");
   __shared__ int32_t hist[16][kBins];
@@ -1023,8 +1033,9 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
       // The (batch, head)s start on different queues: one of fewer than kNumQueues items does not
       // fill them all.
       const uint32_t h0 = head_at[bh[c]], head = head_at[bh[c] + 1] - h0;
-      const uint32_t range = (uint32_t)(((uint64_t)(at[c] - h0) * kNumQueues) / head);
-      const int32_t cls = (int32_t)((uint32_t)cnt[c] * kRankClasses / (uint32_t)(mx + 1));
+      const uint32_t range = whole ? 0 : (uint32_t)(((uint64_t)(at[c] - h0) * kNumQueues) / head);
+      const uint32_t len = whole ? head / per_head - kItemOverhead : (uint32_t)cnt[c];
+      const int32_t cls = (int32_t)(len * kRankClasses / (uint32_t)(mx + 1));
       bin[c] = (int32_t)((range + bh[c]) % kNumQueues) * kRankClasses + kRankClasses - 1 - cls;
       atomicAdd(&hist[wave][bin[c]], 1);
     }
@@ -1624,7 +1635,8 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   int32_t* starts = has_starts(g) ? (int32_t*)(ws + wl.starts) : nullptr;
   if (ranked(g, n_items)) {
     hipLaunchKernelGGL(psa_rank_kernel, dim3(1), dim3(1024), 0, stream, (const int32_t*)counts, order, queues,
-                       starts, header, done, per_head);
+                       starts, header, done, per_head,
+                       (int32_t)(per_head <= kWholeHead && n_items > kWholeItems && done.n_bh >= kWholeHeads));
     return hipGetLastError();
   }
   const uint32_t* spans = starts ? (const uint32_t*)(ws + wl.spans) : nullptr;

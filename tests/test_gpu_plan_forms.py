@@ -1,7 +1,8 @@
-"""Every query row of a plan is computed exactly once and over its own keys, at the sizes where the
-plan changes its kernels: 128 | 129 blocks (one kernel per head | several), 64 | 65 heads (one block
-of parameters | two), 16384 | 16640 items at block 64 and 2048 | 2080 at block 128 (listed longest
-first | by heads), fewer items than queues, all-equal and all-different rows, batch 2.
+"""Every query row of a plan is computed over its own keys, at the sizes where the plan changes its
+kernels: 128 | 129 blocks (one kernel per head | several), 64 | 65 heads (one block of parameters | two),
+16384 | 16640 items at block 64 and 2048 | 2080 at block 128 (listed longest first | by heads), 255 | 256
+heads of four or five items (spread over the queues | whole), fewer items than queues, all-equal and
+all-different rows, batch 2.
 
 With q = 0 every kept key has weight 1, so the normaliser is the logarithm of the number of kept keys
 and o is the mean of v; outputs start as NaN."""
@@ -38,6 +39,7 @@ CASES = [(1, 4, (4, 8, 256, 0), 128, 128), (1, 4, (4, 8, 256, 1), 128, 128), (1,
          (1, 1, (1, 1, 7, 0), 64, 64), (2, 3, (1, 8, 16, 0), 128, 128), (1, 3, (2, 8, 16, 5), 128, 64),
          (1, 4, (16, 8, 128, 0), 128, 128), (1, 4, (16, 8, 128, 1), 128, 128), (2, 4, (16, 8, 64, 0), 64, 128),
          (1, 64, (3, 8, 24, 3), 64, 64), (2, 65, (3, 8, 24, 3), 64, 64), (1, 65, (3, 4, 11, 0), 128, 128),
+         (1, 256, (1, 8, 64, 0), 64, 128), (2, 130, (1, 8, 80, 9), 64, 64), (1, 257, (1, 5, 77, 0), 128, 128), (1, 255, (1, 8, 64, 0), 64, 64),
          (1, 64, (64, 8, 64, 0), 64, 64), (1, 65, (64, 8, 64, 0), 64, 64),
          (2, 32, (8, 8, 128, 0), 128, 64), (2, 33, (8, 8, 128, 0), 128, 64), (1, 16, (32, 8, 128, 0), 128, 128)]
 
