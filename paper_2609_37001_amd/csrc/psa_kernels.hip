@@ -771,13 +771,14 @@ __global__ __launch_bounds__(1024) void psa_head_plan_kernel(
   constexpr int K = kHeadPlanRows / 64;         // blocks per lane
   constexpr int kTable = 512;                   // axis extents with a table of the distances' tests
   __shared__ int2 c_of[kHeadPlanRows];
-  __shared__ uint32_t sig[kHeadPlanRows];
+  __shared__ uint4 sig4[kHeadPlanRows / 4];     // signatures, compared four at a time
   __shared__ uint64_t key[kHeadPlanRows];       // of the leftover rows, ~0 for the others
   __shared__ int32_t by_rank[kHeadPlanRows];    // leftover rows in their order
   __shared__ int2 list[kHeadPlanRows];          // the pairs in the order of their first rows
   __shared__ uint8_t t_keep[2 * kTable], s_keep[2 * kTable];
   __shared__ int32_t firsts[K];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  uint32_t* const sig = (uint32_t*)sig4;
   const int32_t nb = g.nb, np = pairs_per_head(nb), h = head0 + (int32_t)blockIdx.x;
   const psa_stripe_t m = pc.m[blockIdx.x];
   const AxisTest ta(m.t_w, m.t_o, m.t_s), sa(m.s_w, m.s_o, m.s_s);
@@ -841,7 +842,7 @@ __global__ __launch_bounds__(1024) void psa_head_plan_kernel(
     const uint32_t mine = sig[tid];
     int32_t before = 0;
     for (int32_t j = 0; j < nb; j += 4) {       // (rows past the end come after every real one)
-      const uint4 o = *(const uint4*)&sig[j];
+      const uint4 o = sig4[j / 4];
       const uint32_t os[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
       for (int u = 0; u < 4; u++) {
