@@ -1826,7 +1826,7 @@ __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
       for (int kt = 0; kt < H::KT; kt++) {
         // This lane's keys of group kt are positions r0 + {0..7, 16..23}: one 64-bit word.
         const int r0 = k0 + 32 * kt + 8 * h;
-        const uint32_t win = (uint32_t)((r0 < 64 ? lo : hi) >> (r0 & 63));
+        const uint32_t win = (uint32_t)((BLK == 64 || r0 < 64 ? lo : hi) >> (r0 & 63));
 #pragma unroll
         for (int i = 0; i < 16; i++)
           if (!((win >> (16 * (i >> 3) + (i & 7))) & 1u)) s[kt][i] = -__builtin_inff();
@@ -2270,22 +2270,23 @@ __device__ __forceinline__ void process_pair(const DmaPlan<D, BLK>& plan, int gr
       issue_v(0, block_of(e));
     }
   }
+  // The validity words of a block (one word per 64 positions) are read when its loads are issued, a block
+  // ahead: read where they are needed they put a scalar load into the chain of every block.  Not with
+  // SUB = 2, whose four waves per SIMD hide that load and have no registers left.
+  uint64_t lo_next = ~0ull, hi_next = ~0ull;
+  auto read_masks = [&](int kb) {
+    if constexpr (PAD) {
+      lo_next = masks[SUB == 1 ? 2 * kb : kb];
+      if constexpr (BLK > 64) hi_next = masks[2 * kb + 1];
+    }
+  };
+  if (SUB == 1 && nu > 0) read_masks(block_of(e));
   for (int i = 0; i < nu; i++) {
     const int kb = block_of(e);
     const bool mine = my_row >= 0 && (!SPARSE || SUB > 1 || ((e >> (kEntryRowShift + grp)) & 1));
-    uint64_t lo = ~0ull, hi = ~0ull;
-    bool tail;
-    if constexpr (PAD) {
-      if constexpr (SUB == 1) {
-        lo = masks[2 * kb];
-        hi = masks[2 * kb + 1];
-      } else {
-        lo = masks[kb];
-      }
-      tail = (lo & hi) != ~0ull;
-    } else {
-      tail = (kb + 1) * BLK > n;
-    }
+    if constexpr (SUB > 1) read_masks(kb);
+    const uint64_t lo = lo_next, hi = hi_next;
+    const bool tail = PAD ? (BLK > 64 ? lo & hi : lo) != ~0ull : (kb + 1) * BLK > n;
     wait_dma<0>();                                        // block i, issued a block ago
     __syncthreads();                                      // ... by every wave; block i-1 read
     // The next block's K goes out right after the barrier and its V after this block's first
@@ -2297,6 +2298,7 @@ __device__ __forceinline__ void process_pair(const DmaPlan<D, BLK>& plan, int gr
     if (more) {
       e = entry(i + 1);
       kbn = block_of(e);
+      if constexpr (SUB == 1) read_masks(kbn);
       issue_k((i + 1) & 1, kbn);
     }
     if (mine) {
