@@ -2478,8 +2478,11 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
 // workgroup of the pair engine's shape takes ONE query block; its two groups of waves hold the same
 // rows and take half of every key block each (64 keys at block 128, 32 at block 64), and the two
 // online-softmax states are merged through LDS at the end.  One workgroup per query block, all
-// resident at once, so nothing is scheduled: the time is that of the longest query block, half of
-// what it is as half of a pair.  It needs no pairs and no order from the plan.
+// resident at once up to 256 of them (512 at block 64), so nothing is scheduled: the time is that of
+// the longest query block, half of what it is as half of a pair.  It needs no pairs and no order from
+// the plan.  Up to twice as many run in two rounds; the one thing known of their lengths is that text
+// rows keep every key block, so they start first (3 heads x 17776 tokens with 226 of text, block 64
+// and head dim 64: 266 us in the order of the blocks, 200 with text first).
 // Measured (plan and attention, before the pair engine's plan): 2 heads x 1024 x 64, block 64 35 us ->
 // 28; 2 heads x 4672 x 128, block 128 79 -> 42; 18 dense heads of 1116 x 64 24 -> 17; 1.5 times over
 // 24 drawn calls of this size.
@@ -2518,7 +2521,19 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, gw = wave & (T::kWaves - 1);
   const int grp = __builtin_amdgcn_readfirstlane(wave / T::kWaves);
   const int h = lane >> 5, r32 = lane & 31;
-  const int32_t bh = blockIdx.x / nb, qb = blockIdx.x - bh * nb;
+  // The rows of text keep every key block: all of them first, then the others head by head.
+  int32_t bh, qb;
+  {
+    const int32_t local = SPARSE && expect.n_text > 0 ? (n - expect.n_text) / BLK : nb, global = nb - local;
+    const int32_t first = expect.n_bh * global, i = blockIdx.x;
+    if (i < first) {
+      bh = i / global;
+      qb = local + (i - bh * global);
+    } else {
+      bh = (i - first) / local;
+      qb = i - first - bh * local;
+    }
+  }
   const size_t off = (size_t)bh * n * D;
   const __bf16 *kh = k + off, *vh = v + off;
   const int row = qb * BLK + gw * 32 + r32;
@@ -2576,22 +2591,24 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
   const int k0 = grp * HK;
   const uint64_t* masks = (const uint64_t*)(ws + pv.masks);
-  for (int i = 0; i < nu; i++) {
-    uint64_t lo = ~0ull, hi = ~0ull;
-    bool tail;
+  uint64_t lo_next = ~0ull, hi_next = ~0ull;              // a block ahead, as in the pair engine
+  auto read_masks = [&](int b) {
     if constexpr (PAD) {
-      lo = masks[2 * kb];
-      hi = masks[2 * kb + 1];
-      tail = (lo & hi) != ~0ull;
-    } else {
-      tail = (kb + 1) * BLK > n;
+      lo_next = masks[2 * b];
+      if constexpr (BLK > 64) hi_next = masks[2 * b + 1];
     }
+  };
+  if (nu > 0) read_masks(kb);
+  for (int i = 0; i < nu; i++) {
+    const uint64_t lo = lo_next, hi = hi_next;
+    const bool tail = PAD ? (lo & hi) != ~0ull : (kb + 1) * BLK > n;
     wait_dma<0>();                                        // block i, issued a block ago
     __syncthreads();                                      // ... by every wave; block i-1 read
     const int cur = kb;
     const bool more = i + 1 < nu;
     if (more) {
       kb = entry(i + 1);
+      read_masks(kb);
       issue_block<D, BLK>(plan, kh, lds_address(sk[(i + 1) & 1]), kb, n);
     }
     f32x16 s[H::KT];
