@@ -1821,19 +1821,19 @@ __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
   const int h = lane >> 5, g = lane >> 4, j16 = lane & 15;
   if (tail) {
     asm volatile("" ::: "memory");        // keep the mask a branch taken only by partial tiles
+    int hh = h;
+    if constexpr (D == 64) asm volatile("" : "+v"(hh));       // formed here, not kept in a register
     if constexpr (PAD) {
 #pragma unroll
       for (int kt = 0; kt < H::KT; kt++) {
         // This lane's keys of group kt are positions r0 + {0..7, 16..23}: one 64-bit word.
-        const int r0 = k0 + 32 * kt + 8 * h;
+        const int r0 = k0 + 32 * kt + 8 * hh;
         const uint32_t win = (uint32_t)((BLK == 64 || r0 < 64 ? lo : hi) >> (r0 & 63));
 #pragma unroll
         for (int i = 0; i < 16; i++)
           if (!((win >> (16 * (i >> 3) + (i & 7))) & 1u)) s[kt][i] = -__builtin_inff();
       }
     } else {
-      int hh = h;
-      if constexpr (D == 64) asm volatile("" : "+v"(hh));     // formed here, not kept in a register
       const int kbase = kb * BLK + k0 + 8 * hh;
 #pragma unroll
       for (int kt = 0; kt < H::KT; kt++)
