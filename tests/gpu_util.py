@@ -140,6 +140,30 @@ def torch():
     return t
 
 
+def engine(n_bh, nb, block, full=False):
+    """Which engine a sparse call runs on (the library's rule, compared with it in test_rules.py):
+    "split", one workgroup per query block, or "pairs".  full: every head keeps every block."""
+    unit = 128 // block
+    split = n_bh * nb <= 256 * unit
+    if not split and not full:
+        split = n_bh * nb <= 512 * unit and (block == 64 or nb == 1 or nb > 8)
+    return "split" if split else "pairs"
+
+
+def listed_by_heads(n_bh, nb, block):
+    """Whether the plan of a pairs call is too long to be listed longest first."""
+    return n_bh * ((nb + 1) // 2) > (16384 if block == 64 else 2048)
+
+
+def copies_for(n_bh, nb, block, by_heads=False):
+    """How many times n_bh (batch, head) problems have to be repeated to run as pairs (by_heads: and
+    be listed by heads)."""
+    r = 1
+    while engine(n_bh * r, nb, block) != "pairs" or (by_heads and not listed_by_heads(n_bh * r, nb, block)):
+        r += 1
+    return r
+
+
 @functools.lru_cache(maxsize=2)
 def device_qkv(name):
     """Q, K, V of workload `name` on cuda:0 as bf16 [B, H, N, d]."""

@@ -1,7 +1,8 @@
 """The base that the softmax weights are taken from, against the oracle: scores that rise or fall by
 tens along the sequence (the base moves many times, or the first keys outweigh all later ones),
 scores that are all far below zero or above it, at sequence ends that leave the second half of the
-last 128-key block partly filled or empty."""
+last 128-key block partly filled or empty.  On the split engine (its halves of a block) and, with the
+heads repeated, on the pair engine (steps of 64 keys)."""
 import numpy as np
 import pytest
 
@@ -26,10 +27,11 @@ SHAPES = {"rising": lambda x: 90 * x, "falling": lambda x: -90 * x, "low": lambd
           "high": lambda x: 0 * x + 150, "steps": lambda x: 40 * np.floor(5 * x)}
 
 
+@pytest.mark.parametrize("engine", ["split", "pairs"])
 @pytest.mark.parametrize("nt", [0, 1, 65])
 @pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("shape", sorted(SHAPES))
-def test_scores_far_from_zero(shape, d, block, nt):
+def test_scores_far_from_zero(shape, d, block, nt, engine):
     f, hh, ww = 4, 8, 40                     # 1280 video tokens: ten blocks of 128
     n = f * hh * ww + nt
     rng = np.random.default_rng([11, d, block, nt])
@@ -40,9 +42,13 @@ def test_scores_far_from_zero(shape, d, block, nt):
     k[..., 0] = SHAPES[shape](np.arange(n) / n)
     q, k, v = (bf16_round(x) for x in (q, k, v))
     grid = (f, hh, ww, nt)
-    o, lse = psa.attention_fwd(dev(q), dev(k), dev(v), grid, block, PARAMS, scale, return_lse=True)
-    gu.torch().cuda.synchronize()
     keep = oracle.blockmap(PARAMS, f, hh, ww, nt, block)
+    r = gu.copies_for(len(PARAMS), keep.shape[1], block) if engine == "pairs" else 1
+    assert gu.engine(r * len(PARAMS), keep.shape[1], block) == engine
+    o, lse = psa.attention_fwd(*(dev(x).repeat(1, r, 1, 1) for x in (q, k, v)), grid, block, PARAMS * r, scale,
+                               return_lse=True)
+    gu.torch().cuda.synchronize()
+    o, lse = o[:, -len(PARAMS):], lse[:, -len(PARAMS):]
     par = gu.compare_all(q, k, v, keep, block, scale, o.float().cpu().numpy(), lse.cpu().numpy())
     # Where few keys carry the weight P's rounding does not average out: a row is off by up to
     # 2^-8 (P) + 2^-9 (O) of its values' size, which may partly cancel in O; the normaliser's bound

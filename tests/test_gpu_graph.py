@@ -19,13 +19,19 @@ def dev(x):
     return t.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to("cuda:0").bfloat16()
 
 
-@pytest.mark.parametrize("block", [64, 128])
-def test_graph_replays_match_eager(block):
+@pytest.mark.parametrize("copies", [1, 13, 40])
+@pytest.mark.parametrize("block,d", [(64, 128), (128, 128), (64, 64), (128, 64)])
+def test_graph_replays_match_eager(block, d, copies):
+    """3 heads run on the split engine; of 39 (390 blocks of 128) the plan's density chooses the engine and
+    a run launches both; 120 run on pairs, with the plan's order, re-armed queues and, dense, armed ones."""
     torch = gu.torch()
-    f, hh, ww, nt, d = 3, 16, 24, 40, 128
+    f, hh, ww, nt = 3, 16, 24, 40
     n = f * hh * ww + nt
     grid = (f, hh, ww, nt)
-    params = [(1, 0, 2, 2, 0, 3), (2, 1, INF, 1, 0, INF), (1, 0, INF, 1, 0, INF)]
+    params = [(1, 0, 2, 2, 0, 3), (2, 1, INF, 1, 0, INF), (1, 0, INF, 1, 0, INF)] * copies
+    nb = -(-n // block)
+    assert [gu.engine(len(params), nb, block, full) for full in (False, True)] == {
+        1: ["split", "split"], 13: ["split", "pairs"], 40: ["pairs", "pairs"]}[copies]
     rng = np.random.default_rng(block)
     q, k, v = (dev(bf16_round(rng.standard_normal((1, len(params), n, d)).astype(np.float32)))
                for _ in range(3))

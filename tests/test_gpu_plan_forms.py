@@ -1,11 +1,12 @@
 """Every query row of a plan is computed over its own keys, at the sizes where the plan changes its
 kernels: 128 | 129 blocks (one kernel per head | several), 64 | 65 heads (one block of parameters | two),
 16384 | 16640 items at block 64 and 2048 | 2080 at block 128 (listed longest first | by heads), 255 | 256
-heads of four or five items (spread over the queues | whole), fewer items than queues, all-equal and
-all-different rows, batch 2.
+heads of four or five items (spread over the queues | whole), fewer items than queues, the largest number
+of blocks, all-equal and all-different rows, batch 2.
 
-With q = 0 every kept key has weight 1, so the normaliser is the logarithm of the number of kept keys
-and o is the mean of v; outputs start as NaN."""
+With q = 0 every kept key has the same weight, so the normaliser is the logarithm of the number of kept
+keys and o is the mean of v, which is +1 or -1 by (batch, head, key block, channel): a block too many, too
+few, or of another head changes it.  Outputs start as NaN."""
 import numpy as np
 import pytest
 
@@ -40,12 +41,13 @@ CASES = [(1, 4, (4, 8, 256, 0), 128, 128), (1, 4, (4, 8, 256, 1), 128, 128), (1,
          (1, 4, (16, 8, 128, 0), 128, 128), (1, 4, (16, 8, 128, 1), 128, 128), (2, 4, (16, 8, 64, 0), 64, 128),
          (1, 64, (3, 8, 24, 3), 64, 64), (2, 65, (3, 8, 24, 3), 64, 64), (1, 65, (3, 4, 11, 0), 128, 128),
          (1, 256, (1, 8, 64, 0), 64, 128), (2, 130, (1, 8, 80, 9), 64, 64), (1, 257, (1, 5, 77, 0), 128, 128), (1, 255, (1, 8, 64, 0), 64, 64),
+         (1, 2, (62, 64, 128, 0), 64, 64), (1, 2, (62, 64, 128, 0), 64, 128), (1, 2, (62, 128, 128, 0), 128, 64),
          (1, 64, (64, 8, 64, 0), 64, 64), (1, 65, (64, 8, 64, 0), 64, 64),
          (2, 32, (8, 8, 128, 0), 128, 64), (2, 33, (8, 8, 128, 0), 128, 64), (1, 16, (32, 8, 128, 0), 128, 128)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=str)
-def test_every_row_once(case):
+def test_every_row_over_its_own_keys(case):
     batch, heads, grid, block, d = case
     f, h, w, nt = grid
     t = gu.torch()
@@ -53,7 +55,8 @@ def test_every_row_once(case):
     params = stripes(heads, f, -(-(h * w) // block), heads)
     gen = t.Generator(device="cuda").manual_seed(5)
     k = t.randn((batch, heads, n, d), generator=gen, device="cuda", dtype=t.bfloat16)
-    v = t.full_like(k, 0.5)
+    signs = t.randint(0, 2, (batch, heads, -(-n // block), d), generator=gen, device="cuda") * 2.0 - 1.0
+    v = signs.repeat_interleave(block, 2)[:, :, :n].to(k).contiguous()
     q = t.zeros_like(k)
     o = t.full_like(k, float("nan"))
     o, lse, kept = psa.attention_fwd(q, k, v, grid, block, params, out=o, return_lse=True, return_kept_per_row=True)
@@ -69,7 +72,10 @@ def test_every_row_once(case):
     assert np.array_equal(np.isneginf(got), np.broadcast_to(keys == 0, got.shape))
     fin = np.broadcast_to(keys > 0, got.shape)
     assert np.abs(got[fin] - np.broadcast_to(want, got.shape)[fin]).max() <= 2e-5
-    assert t.equal(o, t.from_numpy(np.where(keys > 0, 0.5, 0.0)).to(o)[None, :, :, None].expand_as(o))
+    # o: exact fp32 sums of the weights of one size, one division and one rounding to bf16
+    mean = t.matmul((t.from_numpy(keep).cuda() * t.from_numpy(size).cuda()).float(), signs)
+    mean = (mean / t.from_numpy(keep @ size).cuda().clamp(min=1)[None, :, :, None]).repeat_interleave(block, 2)[:, :, :n]
+    assert bool(((o.float() - mean).abs() <= mean.abs() * 2.0 ** -8 + 1e-6).all())
 
 
 @pytest.mark.parametrize("grid,heads", [((4, 8, 256, 0), 4), ((4, 8, 256, 0), 6), ((4, 8, 256, 9), 8), ((2, 3, 5, 2), 300)])

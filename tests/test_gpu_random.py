@@ -1,7 +1,7 @@
 """Seeded random GPU parity cases: random grids (ragged ends, text), random stripe parameters
-from the paper's ranges, every (head_dim, block) variant, batch 1-2; 1D blocks, the pair engine with
-both pairing orders of leftover query blocks, and 3D PSABlocks.
-Every output row is compared with the oracle."""
+from the paper's ranges, every (head_dim, block) variant, batch 1-2; 1D blocks and 3D PSABlocks (a few
+heads, which run on the split engine), and the pair engine with both pairing orders of leftover query
+blocks.  Every output row of the drawn heads is compared with the oracle."""
 import numpy as np
 import pytest
 
@@ -88,8 +88,9 @@ def slot_major(m):
 
 @pytest.mark.parametrize("seed", range(6))
 def test_random_pair_engine(seed):
-    """Block 128 (the pair engine) on random grids with heads of both leftover pairing orders
-    (index and slot-major), odd and even block counts, text and batch 1-2."""
+    """Block 128 on random grids with heads of both leftover pairing orders (index and slot-major),
+    odd and even block counts, text and batch 1-2; the four heads repeated until the call is large
+    enough for the pair engine.  Every copy equals the first up to the start of its key stream."""
     rng = np.random.default_rng([9, seed])
     d = int(rng.choice([64, 128]))
     f, hh, ww = int(rng.integers(2, 6)), int(rng.integers(4, 17)), int(rng.integers(8, 48))
@@ -101,11 +102,16 @@ def test_random_pair_engine(seed):
     b = int(rng.integers(1, 3))
     scale = float(rng.uniform(0.05, 0.2))
     q, k, v = (bf16_round(rng.standard_normal((b, len(params), n, d)).astype(np.float32)) for _ in range(3))
-    o, lse, kept = psa.attention_fwd(dev(q), dev(k), dev(v), (f, hh, ww, nt), 128, params, scale, return_lse=True,
-                                     return_kept_per_row=True)
-    gu.torch().cuda.synchronize()
     keep = oracle.blockmap(params, f, hh, ww, nt, 128)
-    assert np.array_equal(kept.cpu().numpy(), oracle.kept_per_row(keep))
+    r = gu.copies_for(b * len(params), keep.shape[1], 128)
+    o, lse, kept = psa.attention_fwd(*(dev(x).repeat(1, r, 1, 1) for x in (q, k, v)), (f, hh, ww, nt), 128, params * r,
+                                     scale, return_lse=True, return_kept_per_row=True)
+    gu.torch().cuda.synchronize()
+    assert np.array_equal(kept.cpu().numpy(), oracle.kept_per_row(np.concatenate([keep] * r)))
+    o = o.view(b, r, len(params), n, d)
+    lse = lse.view(b, r, len(params), n)
+    assert bool(((o - o[:, :1]).abs() <= gu.MAX_ABS_TOL).all()) and bool((lse - lse[:, :1]).nan_to_num().abs().max() <= 1e-3)
+    o, lse = o[:, -1], lse[:, -1]
     assert any(slot_major(m) for m in params) and not all(slot_major(m) for m in params)
     compare(q, k, v, keep, scale, o.float().cpu().numpy(), lse.cpu().numpy(), block=128).check(
         "seed %d: n=%d nb=%d d=%d b=%d:" % (seed, n, keep.shape[1], d, b))

@@ -110,7 +110,7 @@ def check_selection(res, refs, bounds):
 
 
 def test_scores_against_oracle_and_selection():
-    """Block 64, head_dim 64 (the one-row engine): the tiny workload's 2 heads x 24 candidates
+    """Block 64, head_dim 64 (a few heads: the split engine): the tiny workload's 2 heads x 24 candidates
     (23 from the paper's candidate space and the full map, whose loss is exactly 0)."""
     cfg = get_config("tiny")                                # 4x16x16, d = 64, block 64, 2 heads
     grid = gu.grid_of(cfg)
@@ -125,10 +125,11 @@ def test_scores_against_oracle_and_selection():
     check_selection(res, refs, bounds)
 
 
-def test_scores_pair_engine_against_oracle():
-    """Block 128, head_dim 128 (the pair engine, the path of the video workloads): 3 heads x 13
-    candidates (12 drawn from the paper's candidate space and the full map) on a 4 x 16 x 32 grid
-    with 40 text tokens (17 blocks; 4 frames of 4 slots and a global text block)."""
+@pytest.mark.parametrize("copies", [1, 11])
+def test_scores_block_128_against_oracle(copies):
+    """Block 128, head_dim 128: 3 heads x 13 candidates (12 drawn from the paper's candidate space and
+    the full map) on a 4 x 16 x 32 grid with 40 text tokens (17 blocks; 4 frames of 4 slots and a global
+    text block); by themselves on the split engine, eleven times on the pair engine."""
     from workloads.params import S_OFFSETS, S_STRIDES, T_OFFSETS, T_STRIDES
     f, hh, ww, nt, block, d, heads, scale = 4, 16, 32, 40, 128, 128, 3, 0.15
     n = f * hh * ww + nt
@@ -145,7 +146,9 @@ def test_scores_pair_engine_against_oracle():
             if m not in seen:
                 seen.append(m)
         cands.append(seen + [(tp, 0, INF, sp, 0, INF)])
-    res = search.score(dev(qn), dev(kn), dev(vn), grid, block, cands, scale)
-    refs, bounds = check_scores(qn, kn, vn, grid, block, scale, cands, res)
+    assert (copies == 1) == (gu.engine(copies * heads, -(-n // block), block) == "split")
+    res = search.score(*(dev(x).repeat(1, copies, 1, 1) for x in (qn, kn, vn)), grid, block, cands * copies, scale)
     assert (res.loss[:, -1] == 0.0).all()
+    res = search.HeadResults(res.candidates[-heads:], res.loss[-heads:], res.sparsity[-heads:])
+    refs, bounds = check_scores(qn, kn, vn, grid, block, scale, cands, res)
     check_selection(res, refs, bounds)

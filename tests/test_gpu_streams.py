@@ -23,11 +23,14 @@ def problem(seed, heads=3, grid=(4, 16, 24, 40), d=128):
                  .to("cuda:0").bfloat16() for _ in range(3))
 
 
-def test_side_stream_calls_equal_current_stream_calls():
+@pytest.mark.parametrize("copies", [1, 14])
+def test_side_stream_calls_equal_current_stream_calls(copies):
+    """One copy of the heads runs on the split engine, fourteen on pairs."""
     torch = gu.torch()
     grid = (4, 16, 24, 40)
-    params = [(1, 0, INF, 2, 0, INF), (2, 1, 3, 1, 0, INF), (4, 0, INF, 1, -1, 3)]
-    q, k, v = problem(41)
+    params = [(1, 0, INF, 2, 0, INF), (2, 1, 3, 1, 0, INF), (4, 0, INF, 1, -1, 3)] * copies
+    assert (copies == 1) == (gu.engine(len(params), 13, 128) == "split")
+    q, k, v = problem(41, heads=len(params))
     ref_o, ref_lse, ref_kept = psa.attention_fwd(q, k, v, grid, 128, params, 0.1, return_lse=True,
                                                  return_kept_per_row=True)
     ref_d = psa.dense_fwd(q, k, v, 128, 0.1)

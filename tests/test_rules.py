@@ -10,12 +10,16 @@ import pytest
 import oracle
 from paper_2609_37001_amd import build
 
+import gpu_util as gu
+
 INF = 0x7FFFFFFF
 MAIN = r"""
 #include <stdio.h>
 #include "psa_launch.h"
-int main() {
-  int f, h, w, text, block;
+int main(int argc, char**) {
+  int f, h, w, text, block, n_bh, nb, full;
+  while (argc > 1 && scanf("%d %d %d %d", &n_bh, &nb, &block, &full) == 4)
+    printf("%d\n", (int)psa::split_plan(n_bh, nb, block, full));
   psa_stripe_t m;
   while (scanf("%d %d %d %d %d %d %d %d %d %d %d", &f, &h, &w, &text, &block, &m.t_w, &m.t_o, &m.t_s, &m.s_w, &m.s_o,
                &m.s_s) == 11) {
@@ -44,9 +48,9 @@ def rules(tmp_path_factory):
     subprocess.run([gxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", build.INCLUDE,
                     "-I", build.CSRC, str(src), "-o", str(exe)], check=True)
 
-    def ask(cases):
+    def ask(cases, *args):
         text = "\n".join(" ".join(str(x) for x in c) for c in cases)
-        out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout.split()
+        out = subprocess.run([str(exe), *args], input=text, capture_output=True, text=True, check=True).stdout.split()
         return [int(x) for x in out]
 
     return ask
@@ -82,3 +86,14 @@ def test_full_plans_are_those_that_keep_every_block(rules):
             assert got == full, c
             seen[got] += 1
     assert min(seen.values()) > 500
+
+
+def test_split_engine_lines(rules):
+    rng = np.random.default_rng(19)
+    cases = [(int(rng.integers(1, 1025)), int(np.exp(rng.uniform(0, 7))), block, full)
+             for block in (64, 128) for full in (0, 1) for _ in range(2000)]
+    cases += [(n, nb, block, full) for block in (64, 128) for full in (0, 1) for nb in (1, 2, 8, 9, 64)
+              for lim in (256, 512) for n in (lim * 128 // block // nb, lim * 128 // block // nb + 1)]
+    got = ["split" if x else "pairs" for x in rules(cases, "split")]
+    assert got == [gu.engine(*c) for c in cases]
+    assert min(got.count("split"), got.count("pairs")) > 500
