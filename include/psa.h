@@ -43,6 +43,10 @@
  *    products accumulated in fp32 (MFMA); softmax statistics in fp32 in the exp2 domain; P
  *    rounded to bf16 before P V, and the normaliser sums the rounded P; O rounded to bf16 (round
  *    to nearest even).  A query row with no kept key gets O = 0 and LSE = -inf.
+ *  - Repeatability: the same call on the same data returns the same bits.  The order in which a row
+ *    sums its key blocks, and so its last bits, may differ between calls of different sizes: batch,
+ *    n_heads, tokens, block and the stripes of all heads decide how the work is split and ordered (up
+ *    to about one query block per CU every block is summed in two halves), in dense calls as well.
  */
 #ifndef PSA_H
 #define PSA_H
@@ -118,12 +122,13 @@ psa_status_t psa_build_blockmap(const psa_stripe_t* params, int32_t n_heads, psa
  * the stripe parameters of each head to the workspace, counts the kept key blocks of every
  * work item with the Algorithm 1 decoder and orders the items.  A work item is a pair of query
  * blocks of one (batch, head) that share one K/V stream, the pairs formed from query blocks with
- * equal kept sets first (the rest in index order) and weighed by the union of the two sets.  Where
- * the query blocks are no more than the GPU runs at once, every query block is an item and nothing is
- * ordered.  Order: short lists longest first; others: items of more than three times the mean work
- * (rows that keep every key block, such as text rows) first, longest first, then the heads longest first, each split into equal-work ranges, one
- * work queue per XCD.  At block 128 the plan of a long list also chooses where each item's K/V stream
- * starts (each row still visits each of its kept blocks once, cyclically ascending from there):
+ * equal kept sets first (the rest in index order) and weighed by the union of the two sets.  Few
+ * query blocks (up to the number the GPU runs at once, and for most maps twice that) are an item
+ * each, without pairs or an order.  Order: short lists longest first; long ones: items of more than
+ * three times the mean work (rows that keep every key block, such as text rows) first, longest first,
+ * then the heads longest first, each split into equal-work ranges, one work queue per XCD.  At block
+ * 128 the plan of a long list also chooses where each item's K/V stream starts (each row still visits
+ * each of its kept blocks once, cyclically ascending from there):
  * where the item started just before it on its queue is predicted to be by then, so that the items
  * in flight on one XCD read the same key blocks at about the same time and its L2 serves them
  * once; pairs that keep every block start at block 0.  The plan
@@ -139,12 +144,14 @@ psa_status_t psa_attention_plan(int32_t batch, int32_t n_heads, psa_grid_t grid,
                                 hipStream_t stream);
 
 /* Sparse attention over a planned workspace (Algorithm 2): a persistent kernel whose
- * workgroups pop work items from the plan's queues (or one workgroup per query block), decode the kept key blocks of each query
- * block (Algorithm 1) and run the tile engine over them.  Arguments as in psa_attention_fwd.  The
+ * workgroups pop work items from the plan's queues (or one workgroup per query block), decode the
+ * kept key blocks of each query block (Algorithm 1) and run the tile engine over them.  Where the
+ * plan's density or balance decides between two kernels, which only the device knows, both are
+ * launched and one returns at once.  Arguments as in psa_attention_fwd.  The
  * workspace must hold a plan made for the same batch, n_heads, grid and block; the kernel checks
  * the plan's header first and, on a mismatch or an unfinished plan, writes nothing (o and lse keep
  * their contents; no error can be returned for a condition found on the device).  The run
- * re-arms the plan's queue counters (a one-thread kernel ahead of the attention kernel) and
+ * re-arms the plan's queue counters (in a small kernel ahead of the attention kernel) and
  * consumes them, so runs over one workspace must not overlap in time (use one workspace per
  * stream). */
 psa_status_t psa_attention_run(const void* q, const void* k, const void* v, void* o,

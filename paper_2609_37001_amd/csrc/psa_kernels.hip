@@ -6,10 +6,14 @@
 //   psa_count_kernel                           kept key blocks of every (batch, head, query block),
 //                                              and kept-set signatures for the pairing
 //   psa_pairing_kernel / psa_paircount_kernel  pairs of query blocks and their work
-//   psa_schedule_kernel                        load-balanced work order split over 8 XCD queues
+//   psa_head_plan_kernel                       all of these for a head of a short sequence
+//   psa_rank_kernel                            work order of a short list: longest first, over 8 XCD
+//                                              queues
+//   psa_schedule_kernel                        ... of a long one: by heads, load-balanced
 //   psa_starts_kernel                          block 128: where each pair item's K/V stream starts
 //   psa_pair_kernel                            persistent block-sparse attention (Algorithm 2) on
 //                                              pairs of query blocks, or dense
+//   psa_split_kernel                           the same for few query blocks, one workgroup each
 //
 // Tile engine (per wave; a workgroup holds 2 BLK rows in 2 BLK/32 wave64s, and PairShape says how
 // many share a CU; head dim D):
@@ -200,8 +204,10 @@ __global__ __launch_bounds__(256) void psa_zero_kernel(int64_t* __restrict__ x, 
 // both axes' tests for every distance of the grid are looked up in LDS, filled once per workgroup;
 // without (an axis of more than kMapExtent positions) each is evaluated by multiplication.
 // The map's bytes alone would take 3 us at 40 heads x 591^2 entries (14 MB); what bounds the kernel
-// are the vector and LDS instructions per entry, 22 us with the counts.  One byte, four divisions
-// and two moduli per thread took 63 us, and the counts of one workgroup per head 403 us more.
+// are the vector and LDS instructions per entry, 22 us with the counts: a column's coordinates still
+// cost two integer divisions for every four rows (the tests of the stripes cost none), and a workgroup
+// begins with those of its rows and two 64-bit ones.  One byte, four divisions and two moduli per
+// thread took 63 us, and the counts of one workgroup per head 403 us more.
 constexpr int kMapRows = 16;
 constexpr int kMapExtent = 4096;
 template <bool GROUPS, bool TABLE>
@@ -1376,8 +1382,10 @@ __global__ __launch_bounds__(1024) void psa_schedule_kernel(const int32_t* __res
 // the same queue is predicted to be by then: the queue is replayed with 32 workgroups taking
 // items as they become free (work = kept blocks + item overhead, the schedule's estimate), and
 // the predecessor's position is placed by linear interpolation over the span of non-global key
-// blocks of their run.  Items that keep every key block start at block 0 (ascending, as in the
-// dense kernel).  The result depends on the plan only, so runs stay deterministic.
+// blocks of their run.  (With two items a pair at head dim 64 four times as many workgroups take
+// halves of the pairs in the same order, which the prediction does not model.)  Items that keep every
+// key block start at block 0 (ascending, as in the dense kernel).  The result depends on the plan
+// only, so runs stay deterministic.
 // One 1024-thread workgroup per queue, over tiles of kStartsTile queue entries; the last
 // workgroup to finish writes the plan header.
 //  0. All waves load the tile's items, kept counts and spans into LDS.
@@ -1559,11 +1567,12 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
 // Whether the plan chooses where the items' K/V streams start (psa_starts_kernel).
 static bool has_starts(const Geometry& g) { return g.block == 128; }
 
-// Whether the items are listed longest first (psa_rank_kernel).  Block 128: up to eight per CU; from
-// there to 32 per CU the order by heads and this one differ by -1.5 to +1.5 %, beyond it is up to 4 %
-// faster (K/V blocks shared in the L2).  Block 64: as long as the kernel can hold the list; 4096 to
-// 8192 items gain 1.5 to 12 % (the schedule kernel takes 35 to 45 us there, this one 10), 8192 to
-// 16384 0.4 to 7.5 %.
+// Whether the items are listed longest first (psa_rank_kernel).  Block 128: up to eight pairs per CU;
+// from there to 32 per CU the order by heads and this one differ by -1.5 to +1.5 %, beyond it is up to
+// 4 % faster (K/V blocks shared in the L2).  Block 64: as long as the kernel can hold the list.  There
+// the run alone is 2 % faster in the mean in this order (48 calls of 57 to 1182 blocks a head, 1112 to
+// 29184 query blocks, 0.985 to 1.11; with 16 blocks a head and more than 8000 in all 2 to 6 % slower),
+// and the plan takes 25 to 35 us less (the schedule kernel 35 to 45 us, this one 10).
 static bool ranked(const Geometry& g, int32_t n_items) { return n_items <= (g.block == 64 ? kRankItems : 2048); }
 
 // Whether one kernel per head makes the whole plan but the order.
@@ -1757,7 +1766,7 @@ struct WaveState {
       for (int i = 0; i < 16; i++) negm[i] = nb;
     }
   }
-  float m;             // running max of the scaled scores
+  float m;             // base of the weights: at or near the running max of the scaled scores
   float l;             // running sum of the bf16-rounded P over this lane's keys
 };
 
@@ -1803,7 +1812,9 @@ __device__ __forceinline__ void qk_half(const WaveState<D, BLK>& st,
 
 // Mask (tail: the block reaches past the sequence end), online-softmax statistics, P^T chunk by
 // chunk and O^T += V^T P^T, for keys [k0, k0 + HK) of block kb.
-//  * The running max moves only when the new max exceeds it by 2^8, so P <= 2^8 (exact).
+//  * The base m of the weights moves only when a weight would exceed 2^8 (then to the row's maximum),
+//    at head dim 64 when one reaches 2 (then to 2^6 above the maximum).  Any base is exact up to the
+//    rounding of the weights, which is relative.
 //  * Accumulator elements 8*(j&1)..+7 of S^T group j/2 are keys 16j + 8h + 0..7: the B operand
 //    of 16-key chunk j.
 //  * V^T operand: within each 16-lane group, source lane 4r+c reads V[key0 + r][d0 + 4c .. +3];
@@ -1843,7 +1854,7 @@ __device__ __forceinline__ void softmax_pv_half(WaveState<D, BLK>& st,
     }
   }
 
-  // s holds S - base with base = -negm (the running max, or 0 before the first kept key).
+  // s holds S - base with base = -negm (m, or 0 before the first kept key).
   // The softmax and its P V form the longest dependent chain of a block; while a wave runs it,
   // it issues ahead of the other wave on its SIMD, whose Q K^T MFMAs fill the gaps (measured:
   // 3 % faster sparse, 2-4 % dense).
@@ -2482,7 +2493,7 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
 // the longest query block, half of what it is as half of a pair.  It needs no pairs and no order from
 // the plan.  Up to twice as many run in two rounds; the one thing known of their lengths is that text
 // rows keep every key block, so they start first (3 heads x 17776 tokens with 226 of text, block 64
-// and head dim 64: 266 us in the order of the blocks, 200 with text first).
+// and head dim 64: 269 us in the order of the blocks, 197 with text first).
 // Measured (plan and attention, before the pair engine's plan): 2 heads x 1024 x 64, block 64 35 us ->
 // 28; 2 heads x 4672 x 128, block 128 79 -> 42; 18 dense heads of 1116 x 64 24 -> 17; 1.5 times over
 // 24 drawn calls of this size.

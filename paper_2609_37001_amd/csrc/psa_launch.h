@@ -87,8 +87,9 @@ struct WorkspaceLayout {
   size_t header;    // PlanHeader
   size_t params;    // psa_stripe_t [n_heads]
   size_t coords;    // int2 [nb]: (frame, slot) of each block, frame = -1 for a global block
-  size_t counts;    // int32 [batch*n_heads*nb]: kept key blocks per work item
-  size_t order;     // int32 [batch*n_heads*nb]: work items in schedule order
+  size_t counts;    // int32 [batch*n_heads*nb], the first batch*n_heads*ceil(nb/2): key blocks kept by
+                    // either row of each pair item
+  size_t order;     // the same: pair items in schedule order
   size_t queues;    // int32 [kQueueWords]: queue boundaries and pop counters
   size_t sigs;      // uint64 [n_heads][nb]: signature of each query block's kept set
   size_t pairs;     // int2 [n_heads][ceil(nb/2)]: query blocks paired into one work item
@@ -101,8 +102,8 @@ struct WorkspaceLayout {
   size_t total;
 };
 
-// Query blocks of one head processed together by the pair engine (BLK = 128): ceil(nb / 2)
-// pairs per head, the second member -1 for a single.
+// Query blocks of one head processed together by the pair engine: ceil(nb / 2) pairs per head, the
+// second member -1 for a single.
 __host__ __device__ inline int32_t pairs_per_head(int32_t nb) { return (nb + 1) / 2; }
 
 // Whether an axis of `extent` positions keeps every distance: the residues of |delta - offset|, which
