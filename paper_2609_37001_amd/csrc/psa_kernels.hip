@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(1024) void psa_rank_kernel(const int32_t* __restric
   }
   __syncthreads();
   if (tid == 0) {
-    done.halves = done.halves && halves_pay(total - kItemOverhead * n, mx, n);
+    queues[kHalvesWord] = halves_pay(total - kItemOverhead * n, mx, n);
     __threadfence();
     *header = done;
   }
@@ -1364,9 +1364,8 @@ __global__ __launch_bounds__(1024) void psa_schedule_kernel(const int32_t* __res
   if (tid <= kNumQueues) queues[tid] = qstart[tid];
   if (tid < kNumQueues) queues[kQueueCounters + tid * kCounterStride] = 0;
   if (tid == 0) {
-    done.halves = done.halves && halves_pay((int64_t)all_work - (int64_t)kItemOverhead * n, max_count, n);
     queues[kStartsDone] = 0;
-    queues[kHalvesWord] = done.halves;
+    queues[kHalvesWord] = halves_pay((int64_t)all_work - (int64_t)kItemOverhead * n, max_count, n);
   }
   __syncthreads();
   if (tid == 0 && write_header) {
@@ -1539,7 +1538,6 @@ __global__ __launch_bounds__(1024) void psa_starts_kernel(
     __threadfence();
     if (atomicAdd(&queues[kStartsDone], 1) == kNumQueues - 1) {
       __threadfence();
-      done.halves = queues[kHalvesWord];
       *header = done;
     }
   }
@@ -1560,7 +1558,6 @@ static PlanHeader plan_header(const Geometry& g, int32_t batch, int32_t n_heads)
   h.pbt = g.pbt;
   h.pbh = g.pbh;
   h.pbw = g.pbw;
-  h.halves = 0;
   return h;
 }
 
@@ -1593,7 +1590,6 @@ hipError_t launch_plan(const ParamChunk* chunks, const Geometry& g, int32_t batc
   const bool split = split_plan(batch * n_heads, g.nb, g.block, full);
   PlanHeader done = plan_header(g, batch, n_heads);
   if (split_by_density(batch * n_heads, g.nb, g.block) && full) done.magic |= kPlanFull;
-  done.halves = halves_possible(g.block, n_items, g.nb);      // narrowed by the work the kernels count
   hipError_t e;
   if (blocks3d) {
     hipLaunchKernelGGL(psa_tiles3d_kernel, dim3((g.nb + 3) / 4), dim3(256), 0, stream, g, coords,
@@ -2388,7 +2384,7 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(PairSha
     // A workspace without a finished plan for exactly these sizes is left alone.
     if (!plan_matches(*header, expect)) return;
     // Of the two shapes of head dim 64 at block 128 the plan has chosen one.
-    if (D == 64 && BLK * SUB == 128 && (header->halves != 0) != (SUB == 2)) return;
+    if (D == 64 && BLK * SUB == 128 && (queues[kHalvesWord] != 0) != (SUB == 2)) return;
   }
   const int32_t n_heads = expect.n_heads, n = expect.n, nb = expect.nb;
   const int32_t np = pairs_per_head(nb), n_items = expect.n_bh * np;

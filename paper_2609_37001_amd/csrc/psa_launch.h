@@ -62,8 +62,6 @@ struct PlanHeader {
   int32_t n;
   int32_t frames, height, width, n_text;
   int32_t pbt, pbh, pbw;
-  int32_t halves;   // whether runs of head dim 64 at block 128 take each pair as two items (set by the
-                    // plan; not one of the sizes a run compares)
 };
 
 // Layout of the queue area (int32 words): kNumQueues + 1 boundaries in the first 128-byte line,
@@ -75,7 +73,8 @@ constexpr int kQueueWords = kQueueCounters + kNumQueues * kCounterStride;
 // Word of the first line (after the boundaries) counting the finished workgroups of the plan's
 // last kernel (psa_starts_kernel).
 constexpr int kStartsDone = 16;
-// Another one holding PlanHeader::halves until that kernel writes the header.
+// Another one: whether runs of head dim 64 at block 128 take each pair as two items (halves_pay), set by
+// the plan.
 constexpr int kHalvesWord = 17;
 static_assert(kStartsDone > kNumQueues && kHalvesWord < kQueueCounters, "free words of the first line");
 
@@ -177,7 +176,8 @@ constexpr int32_t kHalvesMean = 6;
 __host__ __device__ inline bool halves_pay(int64_t work, int64_t longest, int64_t n_items) {
   return work * kHalvesUnit >= kHalvesShare * longest && work >= kHalvesMean * n_items;
 }
-// Whether any plan of these sizes can pass that line (every item keeping every block).
+// Whether any plan of these sizes can pass that line (every item keeping every block): where this says
+// no, no plan's word says yes.
 inline bool halves_possible(int32_t block, int64_t n_items, int32_t nb) {
   return block == 128 && halves_pay(n_items * nb, nb, n_items);
 }

@@ -126,14 +126,18 @@ def test_full_by_text_same_bits_as_dense(d, grid, stripe, heads):
         assert not t.equal(lse, dense_lse)
 
 
-HALVES_WORD = 13                                # of the plan header, after the sizes
+def halves_word(ws, heads, nb):
+    """The word of a plan's queue area that names the shape of head dim 64 at block 128."""
+    up = lambda x: (x + 255) // 256 * 256
+    at = up(256 + 24 * heads) + up(8 * nb) + 2 * up(4 * heads * nb)         # header, stripes, coordinates, counts, order
+    return ws.tensor[at + 4 * 17:at + 4 * 18].view(gu.torch().int32)
 
 
 @pytest.mark.parametrize("pb", [None, (2, 8, 8), (1, 8, 32)])
 @pytest.mark.parametrize("nt,text_rows", [(0, False), (65, False), (130, True)])
 def test_both_shapes_of_head_dim_64_give_the_same_bits(pb, nt, text_rows):
     """At head dim 64 and block 128 the plan chooses between one item and two per pair; a run does what
-    its header says, on either layout, with the same bits, and some heads are compared with the oracle.
+    the plan says, on either layout, with the same bits, and some heads are compared with the oracle.
     The long rows of text at low density choose one item, full rows two."""
     t = gu.torch()
     f, h, w, d, heads = 5, 14, 45, 64, 40
@@ -159,7 +163,7 @@ def test_both_shapes_of_head_dim_64_give_the_same_bits(pb, nt, text_rows):
             lse = t.stack([t.from_numpy(oracle.from_blocks(lse[0, i].cpu().numpy()[:, None], f, h, w, nt, pb)[:, 0])
                            for i in range(heads)])[None]
             return psa.from_blocks(o, grid, pb), lse
-    word = ws.tensor.view(t.int32)[HALVES_WORD:HALVES_WORD + 1]
+    word = halves_word(ws, heads, -(-(n if pb is None else psa.blocked_tokens(grid, pb)) // 128))
     assert int(word) == (0 if text_rows else 1)
     o, lse = go()
     word.fill_(1 - int(word))
