@@ -309,6 +309,8 @@ def utilisation_rows(sq_dir, tcc_dir, trace_dir, label):
     rows = []
     for k in sorted(sq):
         a, b, t = sq[k], tcc[k], dur[k]
+        if a["SQ_INSTS_MFMA"] == 0:                    # a launch that leaves the run to another kernel
+            continue
         cyc = a["GRBM_GUI_ACTIVE"] / 8.0
         rows.append("| %s | %s | %.2f | %.2f | %.3f | %.1f | %.2f | %.3f | %.0f | %.3f |" % (
             label, k, t * 1e3, cyc / t / 1e9, a["SQ_VALU_MFMA_BUSY_CYCLES"] / (cyc * 1024),
