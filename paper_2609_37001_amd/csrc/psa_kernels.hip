@@ -28,7 +28,8 @@
 //     transpose read (ds_read_b64_tr_b16).
 //   * K and V fill LDS by direct global->LDS 16-byte loads (global_load_lds_dwordx4): a double
 //     buffer shared by the two query blocks of a pair, one barrier per block.  16-byte chunks are
-//     XOR-swizzled per row so both the K reads and the transposed V reads are bank-conflict free.
+//     XOR-swizzled per row so both the K reads and the transposed V reads are bank-conflict free at
+//     head dim 128 (see swz).
 //   * Softmax in the exp2 domain: Q is multiplied by scale*log2(e) once, and the S^T
 //     accumulators start at -m, so the MFMAs deliver the exponent directly; m is raised lazily
 //     (only when a weight would reach 2^8, at head dim 64 2), which is exact.
@@ -1680,7 +1681,8 @@ struct Tile {
 // chunk; transposed V reads touch 4 consecutive rows r0..r0+3 at 4 consecutive chunks (16 lanes
 // per cycle: 2 chunks).  Within a quad of rows, bits (1,2) and bits (2,3) of the swizzle are
 // both all distinct; row bits 2 and 3 flip bits 1 and 0.  Every one of these access groups then
-// hits distinct banks whether the LDS serves 128 or 256 bytes per clock.
+// hits distinct banks whether the LDS serves 128 or 256 bytes per clock.  The 8 chunks of D = 64 take
+// the low three bits, for which this does not hold: half of its LDS cycles are bank conflicts.
 template <int CPR>
 __device__ __forceinline__ int swz(int row) {
   const int i = row & 3;
@@ -2066,13 +2068,13 @@ __global__ __launch_bounds__(64) void psa_rearm_kernel(int32_t* __restrict__ que
 //     query block had a workgroup of two waves, two of those shared a CU -- one wave per SIMD -- and
 //     steps were 32 keys: 12 heads x 32760 tokens took 2.77 ms against 1.79 ms, the Wan 2.1 14B rate
 //     on large grids is 1.09 PFLOP/s against 0.68.
-//   * head dim 64: half the MFMA work per score for the same softmax, so the VALU bounds it and
-//     waves matter more than registers: four per SIMD (128 registers each, 32 KB + list per
-//     workgroup).  32 heads x 17776 tokens, block 64: 1.57 ms with one wave per SIMD, 0.95 with
-//     two, 0.90 with three, 0.85 with four.  Where there is enough work per CU (halves_pay) block
-//     128 runs on the same four-wave workgroups (SUB = 2): a work item of the plan's pairs is two
-//     parts, one query block each, whose halves are the two groups' rows and whose 128-key blocks
-//     are two entries of 64 keys.
+//   * head dim 64: half the MFMA work per score for the same softmax.  No unit alone bounds it (of the
+//     cycles VALU 0.64, LDS 0.51, half of that bank conflicts, MFMA 0.50), so waves matter more than
+//     registers: four per SIMD (128 registers each, 32 KB + list per workgroup).  32 heads x 17776
+//     tokens, block 64: 1.57 ms with one wave per SIMD, 0.95 with two, 0.90 with three, 0.85 with
+//     four.  Where there is enough work per CU (halves_pay) block 128 runs on the same four-wave
+//     workgroups (SUB = 2): a work item of the plan's pairs is two parts, one query block each, whose
+//     halves are the two groups' rows and whose 128-key blocks are two entries of 64 keys.
 //   * head dim 64, block 128, eight waves: one workgroup per CU (two waves per SIMD at 167 registers;
 //     four waves mean 128 and spill 37, 1.5 times as long), where there is not, and for dense calls of
 //     few items (launch_dense).
