@@ -2535,19 +2535,13 @@ __global__ __launch_bounds__(BLK * 4) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, gw = wave & (T::kWaves - 1);
   const int grp = __builtin_amdgcn_readfirstlane(wave / T::kWaves);
   const int h = lane >> 5, r32 = lane & 31;
-  // The rows of text keep every key block: all of them first, then the others head by head.
-  int32_t bh, qb;
-  {
-    const int32_t local = SPARSE && expect.n_text > 0 ? (n - expect.n_text) / BLK : nb, global = nb - local;
-    const int32_t first = expect.n_bh * global, i = blockIdx.x;
-    if (i < first) {
-      bh = i / global;
-      qb = local + (i - bh * global);
-    } else {
-      bh = (i - first) / local;
-      qb = i - first - bh * local;
-    }
-  }
+  // The rows of text keep every key block: all of them first, then the others head by head.  (One
+  // division and no branch: behind one, the loads of the arguments below wait for it.)
+  const int32_t local = SPARSE && expect.n_text > 0 ? (n - expect.n_text) / BLK : nb;
+  const int32_t first = expect.n_bh * (nb - local);
+  const bool text = (int32_t)blockIdx.x < first;
+  const int32_t rank = text ? blockIdx.x : blockIdx.x - first, rows = text ? nb - local : local;
+  const int32_t bh = rank / rows, qb = (text ? local : 0) + rank - bh * rows;
   const size_t off = (size_t)bh * n * D;
   const __bf16 *kh = k + off, *vh = v + off;
   const int row = qb * BLK + gw * 32 + r32;
